@@ -219,6 +219,12 @@ struct Chi0Buf {
     int *iters, *status, *refine;
     double* omega_v;  // per trial vector of a chunk: its frequency
     int* order;       // per system of a chunk: dispatch order
+    // real-form COCG (FP64 solves on grids with a launch shape): the right-hand sides and the
+    // solver's state pool, both inside the buffers above
+    bool real_form;
+    double* rhs;
+    double* pool;
+    size_t pool_bytes;
     double2* dbuf;  // backward only
     // host-driven solver (RPA_FLAG_PRECOND or cocg_block >= 2): split complex vectors,
     // per-system scalars, the 1D eigenbases of the preconditioner and the mean of V_loc;
@@ -317,15 +323,31 @@ void carve_chi0(Carver& cv, const Grid& g, int ns, int nvec, const Opts& o, bool
     b.pa = cv.take<char>(size_t(S) * nd * cplx);
     b.pb = cv.take<char>(size_t(S) * nd * cplx);
     b.xlo = b.mixed ? cv.take<char>(size_t(S) * nd * 8) : nullptr;
+    // Real-form COCG keeps its right-hand sides in r (mixed buffers: in r_hi) and its pool of
+    // slots behind them, up to the end of the direction vectors; launches of few systems get
+    // the rest of their slots here.
+    b.real_form = !b.precond && rcocg_fits(g);
+    b.rhs = nullptr;
+    b.pool = nullptr;
+    b.pool_bytes = 0;
+    if (b.real_form) {
+        const size_t skip = b.mixed ? 0 : (size_t(S) * nd * 8 + 255) / 256 * 256;
+        const size_t start = cv.used - size_t(S) * nd * (b.mixed ? 32 : 48) + skip;
+        b.pool_bytes = rcocg_pool_bytes(g, S) + 512;   // 512: see the restart of broken-down systems
+        const size_t first = start / 256 * 256 + 256;
+        if (first + b.pool_bytes > cv.used) cv.take<char>(first + b.pool_bytes - cv.used);
+        if (cv.base) b.pool = reinterpret_cast<double*>(cv.base + first);
+    }
     b.x = cv.take<char>(size_t(S) * nd * (b.x_complex ? 16 : 8));
     b.rhi = b.mixed ? cv.take<double>(2 * size_t(S) * nd) : nullptr;
+    if (b.real_form) b.rhs = b.mixed ? b.rhi : static_cast<double*>(b.r);
     b.b2 = b.mixed ? cv.take<double>(S) : nullptr;
     b.vloc32 = b.mixed ? cv.take<float>(size_t(nd)) : nullptr;
     b.iters = cv.take<int>(S);
     b.status = cv.take<int>(S);
     b.refine = cv.take<int>(S);
     b.omega_v = cv.take<double>(b.chunk);
-    b.order = cv.take<int>(S);
+    b.order = cv.take<int>(size_t(S) + 1);
     b.dbuf = with_d ? cv.take<double2>(size_t(ns) * S) : nullptr;
     if (b.precond) {
         const size_t blk = 2 * size_t(S) * nd;
@@ -617,6 +639,30 @@ bool fp64_in_mixed(const Chi0Buf& b, const Opts& o, double w) {
     return b.mixed && w < o.mixed_min_omega;
 }
 
+// A real-form launch on n systems of the chunk's buffers (real solutions).
+RcocgLaunch real_launch(const rpa_cell* cell, const Grid& g, const Opts& o, const Chi0Buf& b,
+                        int n) {
+    RcocgLaunch R{};
+    R.g = g;
+    R.nsys = n;
+    R.ns = cell->n_occ;
+    R.vloc = cell->v_loc;
+    R.eps = b.eps;
+    R.omega_v = b.omega_v;
+    R.order = b.order;
+    R.counter = b.order + n;
+    R.tol = o.cocg_tol;
+    R.max_iter = o.cocg_max_iter;
+    R.rhs = b.rhs;
+    R.x = b.x;
+    R.pool = b.pool;
+    R.pool_bytes = b.pool_bytes;
+    R.iters = b.iters;
+    R.status = b.status;
+    R.refinements = b.mixed ? b.refine : nullptr;
+    return R;
+}
+
 // Solve the Sternheimer systems of the trial vectors j0 .. j0+nv-1 (columns of U, which
 // points at column j0), each at its own frequency h.omega[j].  With mixed buffers and
 // fp64_run, the run solves in FP64 inside the mixed state: the complex128 residual goes in
@@ -630,7 +676,10 @@ int solve_chunk(const rpa_cell* cell, const Grid& g, const Opts& o, const Chi0Bu
     const int64_t nd = g.nd();
     const double dV = g.h * g.h * g.h;
     RPA_HIP(launch_proj_coeff(nd, ns, nv, dV, cell->psi, U, b.part, b.nsplit, b.coeff, s));
-    if (b.mixed && fp64_run) {
+    const bool real_form = b.real_form && (!b.mixed || fp64_run) && !cocg_shape_forced();
+    if (real_form) {
+        RPA_HIP(launch_proj_rhs_real(nd, ns, nv, cell->psi, U, b.coeff, b.rhs, s));
+    } else if (b.mixed && fp64_run) {
         RPA_HIP(launch_proj_rhs<double>(nd, ns, nv, cell->psi, U, b.coeff, b.rhi, nullptr, s));
     } else if (b.mixed) {
         RPA_HIP(launch_proj_rhs<float>(nd, ns, nv, cell->psi, U, b.coeff,
@@ -702,10 +751,21 @@ int solve_chunk(const rpa_cell* cell, const Grid& g, const Opts& o, const Chi0Bu
         return RPA_OK;
     }
     dispatch_order(cell, nv, j0, h);
+    h.order.push_back(0);          // the real-form kernel's position counter
     RPA_HIP(hipMemcpyAsync(b.omega_v, h.om_chunk.data(), sizeof(double) * nv,
                            hipMemcpyHostToDevice, s));
-    RPA_HIP(hipMemcpyAsync(b.order, h.order.data(), sizeof(int) * ns * nv, hipMemcpyHostToDevice,
-                           s));
+    RPA_HIP(hipMemcpyAsync(b.order, h.order.data(), sizeof(int) * h.order.size(),
+                           hipMemcpyHostToDevice, s));
+    if (real_form) {
+        RcocgLaunch R = real_launch(cell, g, o, b, ns * nv);
+        R.x_complex = x_complex;
+        hipEvent_t e0, e1;
+        RPA_CHECK(timer_events(&e0, &e1));
+        RPA_HIP(hipEventRecord(e0, s));
+        RPA_HIP(launch_rcocg(R, s));
+        RPA_HIP(hipEventRecord(e1, s));
+        return RPA_OK;
+    }
     CocgLaunch L{};
     L.g = g;
     L.nsys = ns * nv;
@@ -786,58 +846,84 @@ int continue_capped(const rpa_cell* cell, const Grid& g, const Opts& o, const Ch
                     int nv, Chi0Host& h, SolveTally& t, hipStream_t s) {
     if (!b.mixed) return RPA_OK;
     const int S = cell->n_occ * nv;
-    std::vector<int> capped;
-    for (int i = 0; i < S; ++i)
-        if (h.st[i] == 1 || h.st[i] == 2) capped.push_back(i);
-    if (capped.empty()) return RPA_OK;
-    RPA_HIP(hipMemcpyAsync(b.order, capped.data(), sizeof(int) * capped.size(),
-                           hipMemcpyHostToDevice, s));
-    CocgLaunch L{};
-    L.g = g;
-    L.nsys = int(capped.size());
-    L.ns = cell->n_occ;
-    L.vloc = cell->v_loc;
-    L.eps = b.eps;
-    L.omega = h.om_chunk[0];
-    L.omega_v = b.omega_v;
-    L.order = b.order;
-    L.tol = o.cocg_tol;
-    L.max_iter = o.cocg_max_iter;
-    L.r = b.rhi;
-    L.pa = b.r;
-    L.pb = b.pb;
-    L.x = b.x;
-    L.x_complex = true;
-    L.iters = b.iters;
-    L.status = b.status;
-    L.fp32 = false;
-    L.b2 = b.b2;
-    L.x_accum = true;
-    hipEvent_t e0, e1;
-    RPA_CHECK(timer_events(&e0, &e1));
-    RPA_HIP(hipEventRecord(e0, s));
-    RPA_HIP(launch_cocg(L, s));
-    RPA_HIP(hipEventRecord(e1, s));
-    std::vector<int> it(S), st(S);
-    RPA_HIP(hipMemcpyAsync(it.data(), b.iters, sizeof(int) * S, hipMemcpyDeviceToHost, s));
-    RPA_HIP(hipMemcpyAsync(st.data(), b.status, sizeof(int) * S, hipMemcpyDeviceToHost, s));
-    RPA_HIP(hipStreamSynchronize(s));
-    float ms = 0.0f;
-    RPA_HIP(hipEventElapsedTime(&ms, e0, e1));
-    t.kernel_ms += ms;
-    t.launches += 1;
-    t.fallbacks += int(capped.size());
-    for (int i : capped) {
-        t.point_iters += double(it[i]) * double(g.nd());
-        t.iters_total += it[i];
-        t.iters_max = std::max(t.iters_max, h.it[i] + it[i]);
-        // counted by tally() from the mixed stage
-        if (h.st[i] == 1)
-            t.unconv -= 1;
-        else
-            t.breakdown -= 1;
-        t.unconv += (st[i] == 1);
-        t.breakdown += (st[i] == 2);
+    // systems that broke down at their first step have x_hi = 0 and r_hi = b: with a real-form
+    // launch shape they are solved afresh, as in the FP64 path
+    std::vector<int> capped, fresh;
+    const bool real_form = b.real_form && !cocg_shape_forced();
+    for (int i = 0; i < S; ++i) {
+        if (h.st[i] != 1 && h.st[i] != 2) continue;
+        (real_form && h.st[i] == 2 && h.it[i] == 1 ? fresh : capped).push_back(i);
+    }
+    for (int pass = 0; pass < 2; ++pass) {
+        std::vector<int>& list = pass == 0 ? fresh : capped;
+        if (list.empty()) continue;
+        const int n = int(list.size());
+        list.push_back(0);             // the real-form kernel's position counter
+        RPA_HIP(hipMemcpyAsync(b.order, list.data(), sizeof(int) * list.size(),
+                               hipMemcpyHostToDevice, s));
+        list.pop_back();
+        hipEvent_t e0, e1;
+        RPA_CHECK(timer_events(&e0, &e1));
+        if (pass == 0) {
+            // right-hand sides packed over r, the pool behind them
+            const int64_t tot = int64_t(S) * g.nd();
+            RPA_HIP(launch_real_part(tot, b.rhi, static_cast<double*>(b.r), s));
+            const size_t skip = (size_t(tot) * sizeof(double) + 511) / 256 * 256;
+            RcocgLaunch R = real_launch(cell, g, o, b, n);
+            R.rhs = static_cast<const double*>(b.r);
+            R.x_complex = true;
+            R.pool += skip / sizeof(double);
+            R.pool_bytes -= skip;
+            R.refinements = nullptr;
+            RPA_HIP(hipEventRecord(e0, s));
+            RPA_HIP(launch_rcocg(R, s));
+        } else {
+            CocgLaunch L{};
+            L.g = g;
+            L.nsys = n;
+            L.ns = cell->n_occ;
+            L.vloc = cell->v_loc;
+            L.eps = b.eps;
+            L.omega = h.om_chunk[0];
+            L.omega_v = b.omega_v;
+            L.order = b.order;
+            L.tol = o.cocg_tol;
+            L.max_iter = o.cocg_max_iter;
+            L.r = b.rhi;
+            L.pa = b.r;
+            L.pb = b.pb;
+            L.x = b.x;
+            L.x_complex = true;
+            L.iters = b.iters;
+            L.status = b.status;
+            L.fp32 = false;
+            L.b2 = b.b2;
+            L.x_accum = true;
+            RPA_HIP(hipEventRecord(e0, s));
+            RPA_HIP(launch_cocg(L, s));
+        }
+        RPA_HIP(hipEventRecord(e1, s));
+        std::vector<int> it(S), st(S);
+        RPA_HIP(hipMemcpyAsync(it.data(), b.iters, sizeof(int) * S, hipMemcpyDeviceToHost, s));
+        RPA_HIP(hipMemcpyAsync(st.data(), b.status, sizeof(int) * S, hipMemcpyDeviceToHost, s));
+        RPA_HIP(hipStreamSynchronize(s));
+        float ms = 0.0f;
+        RPA_HIP(hipEventElapsedTime(&ms, e0, e1));
+        t.kernel_ms += ms;
+        t.launches += 1;
+        t.fallbacks += n;
+        for (int i : list) {
+            t.point_iters += double(it[i]) * double(g.nd());
+            t.iters_total += it[i];
+            t.iters_max = std::max(t.iters_max, h.it[i] + it[i]);
+            // counted by tally() from the mixed stage
+            if (h.st[i] == 1)
+                t.unconv -= 1;
+            else
+                t.breakdown -= 1;
+            t.unconv += (st[i] == 1);
+            t.breakdown += (st[i] == 2);
+        }
     }
     return RPA_OK;
 }

@@ -195,6 +195,8 @@ bool cocg_shape_exists(const Grid& g, bool mixed) {
     return f64 && mx;
 }
 
+bool cocg_shape_forced() { return std::getenv("RPA_COCG_SHAPE") != nullptr; }
+
 hipError_t launch_cocg(const CocgLaunch& L, hipStream_t s) {
     if (L.nsys <= 0) return hipSuccess;
     cocg::Args a{};

@@ -179,6 +179,14 @@ struct StoreRhs {  // r0[s][r] = -(psi_n u_j - acc), complex with zero imaginary
     }
 };
 
+struct StoreRhsReal {  // r0[s][r] = -(psi_n u_j - acc), real
+    const double* psi; const double* U; int64_t nd; int ns; double* r0;
+    __device__ void operator()(int s, int r, int, double acc) const {
+        const int n = s % ns, j = s / ns;
+        r0[int64_t(s) * nd + r] = acc - psi[r + nd * n] * U[r + nd * j];
+    }
+};
+
 // ------------------------------------------------------------------ Gram and rotation
 struct ColT {  // A(i, k) = A[k + nd i]   (operand transposed)
     static constexpr bool k_contig = true;
@@ -445,6 +453,12 @@ template hipError_t launch_proj_rhs<double>(int64_t, int, int, const double*, co
                                             const double*, double*, double*, hipStream_t);
 template hipError_t launch_proj_rhs<float>(int64_t, int, int, const double*, const double*,
                                            const double*, float*, double*, hipStream_t);
+
+hipError_t launch_proj_rhs_real(int64_t nd, int ns, int nvec, const double* psi, const double* U,
+                                const double* coeff, double* r0, hipStream_t s) {
+    return run_gemm(ns * nvec, int(nd), ns, 1, 0, CoeffT{coeff, ns}, PsiKN{psi, nd},
+                    StoreRhsReal{psi, U, nd, ns, r0}, s);
+}
 
 hipError_t launch_gram(int64_t nd, int m, const double* A, const double* B, double* part,
                        int nsplit, double* G, hipStream_t s) {

@@ -131,6 +131,35 @@ template <typename T>
 hipError_t launch_proj_rhs(int64_t nd, int ns, int nvec, const double* psi, const double* U,
                            const double* coeff, T* r0, double* r64, hipStream_t s);
 
+// The same right-hand sides, real (their imaginary part is zero), for launch_rcocg.
+hipError_t launch_proj_rhs_real(int64_t nd, int ns, int nvec, const double* psi, const double* U,
+                                const double* coeff, double* r0, hipStream_t s);
+
+// Batched COCG on real right-hand sides in its real Lanczos form, FP64 (rcocg_kernel.h): one
+// workgroup per system, systems taken from a counter in dispatch order.
+struct RcocgLaunch {
+    Grid g;
+    int nsys, ns;
+    const double* vloc;
+    const double* eps;      // device, ns
+    const double* omega_v;  // device, nsys / ns
+    const int* order;       // device, nsys
+    int* counter;           // device, 0
+    double tol;
+    int max_iter;
+    const double* rhs;      // nsys x N_d real
+    void* x;                // nsys x N_d real (complex if x_complex)
+    bool x_complex;
+    double* pool;           // solver state: rcocg_slots() slots
+    size_t pool_bytes;
+    int *iters, *status, *refinements;   // nsys (refinements: written 0, may be null)
+};
+hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t s);
+// Host-only: whether a launch shape exists for the grid, and the bytes of state pool for nsys
+// systems (0 without a shape).
+bool rcocg_fits(const Grid& g);
+size_t rcocg_pool_bytes(const Grid& g, int nsys);
+
 // Batched COCG, one workgroup per system.  See cocg.hip for the layout.
 struct CocgLaunch {
     Grid g;
@@ -169,6 +198,8 @@ hipError_t launch_cocg(const CocgLaunch& a, hipStream_t s);
 // variant of at most 3 columns per thread and 1024 threads, or row slabs of at least 12 rows
 // with one column per thread), in FP64 and, with `mixed`, also in complex64.  No device call.
 bool cocg_shape_exists(const Grid& g, bool mixed);
+// Whether RPA_COCG_SHAPE forces a shape of this kernel: FP64 solves then take it too.
+bool cocg_shape_forced();
 
 // Static device scratch of the allocation-free entry point (noalloc.hip): its size, and its
 // device address on the current device (looked up once per device with hipGetSymbolAddress).
@@ -215,6 +246,8 @@ hipError_t launch_grad_accum_d(int64_t nd, int ns, int nvec, const double* psi,
 hipError_t launch_scale(int64_t n, double a, double* x, hipStream_t s);
 hipError_t launch_copy(int64_t n, const double* src, double* dst, hipStream_t s);
 hipError_t launch_fill(int64_t n, double v, double* x, hipStream_t s);
+// dst[i] = real part of the interleaved complex src[i]
+hipError_t launch_real_part(int64_t n, const double* src, double* dst, hipStream_t s);
 // dst[i] = float(src[i])
 hipError_t launch_to_float(int64_t n, const double* src, float* dst, hipStream_t s);
 

@@ -1,0 +1,145 @@
+// Launch-shape selection for the real-form COCG kernel (design in rcocg_kernel.h).
+//
+// A shape is (C rows per thread, Z planes per barrier step).  One row per thread up to 1024
+// columns: more rows share LDS reads, but the kernel waits on memory and wants waves (24^3: 26.5
+// ms with C = 1, 34 with 2, 47 with 3).  Two planes per step where n2 is even (26.5 against 28.8
+// ms).  Planes over 1024 points take the fewest rows that fit 1024 threads (40^3: 37.2 ms with C =
+// 2, 40.3 with 3), with one plane per step (two spill: 77 ms).  Planes over 2304 points (and over
+// 2048 unless three rows of 768 threads hold them) have no shape and stay on the complex kernel.
+// RPA_RCOCG_SHAPE="C,Z" forces a shape; RPA_COCG_VERBOSE=1 prints the one launched.
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+
+#include "rcocg_kernel.h"
+
+namespace rpa {
+
+namespace {
+
+using KernelFn = void (*)(rcocg::Args);
+
+struct Variant {
+    int C, Z, bsmax;
+    bool ragged;           // C does not divide n1
+    KernelFn real, cplx;
+};
+
+#define RPA_V(CC, ZZ, BM, RG)                                        \
+    {CC, ZZ, BM, RG, rcocg::rcocg_wg<double, CC, ZZ, BM, RG>,        \
+     rcocg::rcocg_wg<double2, CC, ZZ, BM, RG>}
+const Variant kTable[] = {
+    RPA_V(1, 1, 256, false), RPA_V(1, 1, 512, false),  RPA_V(1, 1, 768, false), RPA_V(1, 1, 1024, false),
+    RPA_V(1, 2, 256, false), RPA_V(1, 2, 512, false),  RPA_V(1, 2, 768, false), RPA_V(1, 2, 1024, false),
+    RPA_V(2, 1, 768, false), RPA_V(2, 1, 1024, false), RPA_V(3, 1, 768, false),
+    RPA_V(2, 1, 768, true),  RPA_V(2, 1, 1024, true),  RPA_V(3, 1, 768, true)};
+#undef RPA_V
+
+struct Shape {
+    const Variant* v = nullptr;
+    int bs = 0, nbuf = 2, rs = 0;
+    size_t lds = 0;
+};
+
+size_t lds_bytes(const Grid& g, int C, int Z, int nbuf, int rs) {
+    return 16 * 3 * sizeof(double) + rcocg::kRing * sizeof(rcocg::Coef) + 16 +
+           size_t(nbuf) * Z * (g.n1 + 11 + C) * rs * sizeof(double);
+}
+
+Shape choose(const Grid& g) {
+    int fC = 0, fZ = 0;
+    if (const char* e = std::getenv("RPA_RCOCG_SHAPE")) std::sscanf(e, "%d,%d", &fC, &fZ);
+    Shape best;
+    double best_cost = 1e30;
+    for (const Variant& v : kTable) {
+        if (g.n2 % v.Z != 0 || (g.n1 % v.C != 0) != v.ragged) continue;
+        if (fC && (v.C != fC || v.Z != fZ)) continue;
+        const int cols = g.n0 * ((g.n1 + v.C - 1) / v.C);
+        const int bs = (cols + 63) / 64 * 64;
+        if (bs > v.bsmax || bs <= v.bsmax - (v.C == 3 ? 512 : 256)) continue;
+        Shape s;
+        s.v = &v;
+        s.bs = bs;
+        s.rs = (g.n0 + 12 + 7) / 8 * 8;
+        s.lds = lds_bytes(g, v.C, v.Z, 2, s.rs);
+        if (s.lds > 150 * 1024) {
+            s.nbuf = 1;
+            s.lds = lds_bytes(g, v.C, v.Z, 1, s.rs);
+        }
+        if (s.lds > 150 * 1024) continue;
+        const double cost = double(bs - cols) / bs + 0.1 * (2 - v.Z) + 0.05 * v.C;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = s;
+        }
+    }
+    return best;
+}
+
+// Workgroups per CU the pool is sized for.
+int per_cu(int bs) { return bs > 512 ? 1 : bs > 320 ? 2 : bs > 192 ? 3 : 4; }
+
+constexpr int kCUs = 256;
+
+}  // namespace
+
+bool rcocg_fits(const Grid& g) { return choose(g).v != nullptr; }
+
+size_t rcocg_pool_bytes(const Grid& g, int nsys) {
+    const Shape s = choose(g);
+    if (!s.v) return 0;
+    const size_t vec = size_t(g.nd()) * sizeof(double);
+    const size_t slots = std::min(nsys, kCUs * per_cu(s.bs));
+    // launches of few systems get 48 B per point and system and keep a shorter ring
+    return std::min(slots * (rcocg::kRing + rcocg::kSlotExtra) * vec, size_t(nsys) * 6 * vec);
+}
+
+hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
+    if (L.nsys <= 0) return hipSuccess;
+    const Shape s = choose(L.g);
+    if (!s.v) return hipErrorInvalidConfiguration;
+    rcocg::Args a{};
+    a.n0 = L.g.n0;
+    a.n1 = L.g.n1;
+    a.n2 = L.g.n2;
+    a.P = L.g.n0 * L.g.n1;
+    double w[7];
+    fd_weights(w);
+    const double ih2 = 1.0 / (L.g.h * L.g.h);
+    a.cw[0] = -0.5 * 3.0 * w[0] * ih2;
+    for (int k = 1; k <= 6; ++k) a.cw[k] = -0.5 * w[k] * ih2;
+    a.vloc = L.vloc;
+    a.eps = L.eps;
+    a.ns = L.ns;
+    a.nsys = L.nsys;
+    a.omega_v = L.omega_v;
+    a.order = L.order;
+    a.counter = L.counter;
+    a.tol2 = L.tol * L.tol;
+    a.max_iter = L.max_iter;
+    a.nd = L.g.nd();
+    a.rhs = L.rhs;
+    a.x = L.x;
+    a.pool = L.pool;
+    a.iters = L.iters;
+    a.status = L.status;
+    a.refinements = L.refinements;
+    a.nbuf = s.nbuf;
+    a.rs = s.rs;
+    a.periodic = L.g.periodic() ? 1 : 0;
+    const KernelFn fn = L.x_complex ? s.v->cplx : s.v->real;
+    const int grid = std::min(L.nsys, kCUs * per_cu(s.bs));
+    const int vecs = int(L.pool_bytes / (size_t(grid) * size_t(a.nd) * sizeof(double)));
+    a.ring = std::min(rcocg::kRing, vecs - rcocg::kSlotExtra);
+    if (a.ring < rcocg::kRingMin) return hipErrorInvalidValue;
+    if (std::getenv("RPA_COCG_VERBOSE"))
+        std::fprintf(stderr, "rcocg shape C=%d Z=%d bs=%d nbuf=%d grid=%d ring=%d lds=%zu\n", s.v->C,
+                     s.v->Z, s.bs, s.nbuf, grid, a.ring, s.lds);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(s.lds));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(s.bs), s.lds, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace rpa

@@ -1,0 +1,496 @@
+// Batched COCG on real right-hand sides (H - eps_n - i omega) x = b, b real, in FP64.
+//
+// H - eps_n is real symmetric and b is real, so every COCG residual is a complex multiple of
+// a real vector: the Krylov basis is the real Lanczos basis of H - eps_n,
+//   w = (A - sigma) v_k - beta_k v_{k-1},  delta = v_k^T w,  alpha_k = sigma + delta,
+//   beta_{k+1}^2 = |w|^2 - delta^2,        v_{k+1} = (w - delta v_k) / beta_{k+1},
+// and the COCG iterate is the Galerkin solution on it, updated through the L D L^T factors of
+// the shifted tridiagonal matrix:
+//   d_k = alpha_k - i omega - beta_k l_k,  l_k = beta_k / d_{k-1},  zeta_k = -l_k zeta_{k-1},
+//   p_k = v_k - l_k p_{k-1},  x_k = x_{k-1} + (zeta_k / d_k) p_k,  |r_k| = beta_{k+1} |zeta_k / d_k|.
+// In exact arithmetic these are the iterates and residual norms of COCG, one product with A per
+// iteration; |Im d_k| >= omega, so the recurrence cannot break down.
+//
+// What bounds it: memory.  COCG on complex vectors moves r, p, x twice through two sweeps
+// (120 B per point-iteration measured at 24^3, 161 B at 48^3).  Here one sweep per iteration
+// reads w and v_k and writes v_{k+1} and w (32 B), and p and x are updated once per m <= kRing
+// iterations from the last m basis vectors, which a ring keeps (8 + 48 / m B per
+// point-iteration).
+//
+//  * sigma is the previous alpha, so |w|^2 - delta^2 does not cancel; where it does (first step,
+//    b close to an eigenvector) the sweep is repeated with sigma = alpha.
+//  * One workgroup owns a system for its whole solve and takes the next one from a counter, in
+//    dispatch order; its vectors live in a slot of the state pool (kRing ring vectors, w, p).
+//  * A sweep marches along z.  A thread owns C consecutive rows of the x-y plane at one x and
+//    keeps planes z-6 .. z+5+Z of v_{k+1} in registers; the current planes are staged in LDS with
+//    ghost columns and rows.  The C rows share their y neighbours: 12 + 12 / C LDS reads per
+//    point instead of 24.
+//  * The queue is carried from sweep to sweep (periodic grids): it starts the next sweep with 12
+//    planes of w instead of 12 planes of w and v.
+//  * Reductions are fixed-order and the operations of a solve depend on the grid alone: results
+//    are bitwise reproducible, whatever slot, ring or launch a system gets.
+//
+// Measured, chi0 block-applies, the two-sweep complex kernel against this one: 24^3, 1024
+// systems, omega 0.02, tol 1e-10: 62.2 -> 26.5 ms (5.4 TB/s); 48^3, 1024 systems, omega 8.8, tol
+// 1e-8: 136 -> 48 ms; 32^3, 2 x 1024 systems with complex solutions: 217 -> 84 ms.
+#pragma once
+
+#include <type_traits>
+
+#include "cocg_kernel.h"
+
+namespace rpa {
+namespace rcocg {
+
+using cocg::ld;
+using cocg::lds_barrier;
+using cocg::st;
+using cocg::uniform;
+using cocg::wg_reduce;
+
+constexpr int kRing = 8;       // most basis vectors kept between two updates of p and x
+constexpr int kRingMin = 2;    // the sweep reads v_k and writes v_{k+1}
+constexpr int kSlotExtra = 3;  // vectors of a slot besides the ring: w, complex p
+
+struct Args {
+    int n0, n1, n2, P;
+    double cw[7];          // cw[k] = -1/2 w_k / h^2 for k >= 1; cw[0] = -1/2 * 3 w_0 / h^2
+    const double* vloc;
+    const double* eps;
+    int ns, nsys;
+    const double* omega_v; // per trial vector j (system s = n + ns j)
+    const int* order;      // the i-th system to start is order[i]
+    int* counter;          // next position in order (0 before the launch)
+    double tol2;
+    int max_iter;
+    int64_t nd;
+    const double* rhs;     // system-major, N_d real each
+    void* x;               // system-major: N_d real (XS = double) or complex (double2)
+    double* pool;          // gridDim.x slots of (ring + kSlotExtra) * N_d doubles
+    int ring;              // basis vectors kept, kRingMin .. kRing
+    int* iters;
+    int* status;
+    int* refinements;      // written 0 per system if not null
+    int nbuf;              // LDS plane buffers (2: one barrier per step, 1: two barriers)
+    int rs;                // LDS row stride in entries, >= n0 + 12
+    int periodic;
+};
+
+__device__ __forceinline__ void global_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// The thread's place in the plane: x = cx, rows y0 .. y0 + C - 1.  Threads past the last row
+// group own no row and read the first columns.  Where C does not divide n1 (ragged), the last
+// group reads the rows past n1 - 1 from their periodic images (zero in a box), which other
+// threads own and store: own(i) says what this thread stages, stores and sums.
+template <int C>
+struct Rows {
+    int cx, y0;
+    unsigned col[C];       // y n0 + x: the only per-thread part of an address
+    bool on, own_[C];
+    template <bool RAG>
+    __device__ bool own(int i) const { return RAG ? own_[i] : on; }
+};
+
+// Ends a group of LDS reads: what was read is consumed here, which bounds the registers held by
+// reads in flight.
+template <int C>
+__device__ __forceinline__ void hold(double (&s)[C]) {
+#pragma unroll
+    for (int i = 0; i < C; ++i) asm volatile("" : "+v"(s[i])::"memory");
+}
+
+// v_{k+1} at a point, with one rounding order wherever it is formed.
+__device__ __forceinline__ double vnext(double cw, double w, double cv, double v) {
+    return __builtin_fma(cw, w, cv * v);
+}
+
+// One sweep: from the lead vectors lw, lv it forms v = cw lw + cv lv plane by plane, stores v to
+// vout, and q = (A - sigma) v - cp lv to wout.  lw may be wout (in place: a plane is read
+// at least 6 planes before it is written; the periodic images read past the top come
+// from vout).  acc = (v.q, q.q, v.v).  With warm = true, Q[0..11] holds the swept vector of the
+// previous sweep (that is lv) on planes -6 .. 5.
+template <int C, int Z, bool RAG>
+__device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* planes,
+                                      double diag0, const double* lw, const double* lv,
+                                      double cw, double cv, double cp, double* vout, double* wout,
+                                      double (&Q)[12 + Z][C], bool warm, double (&acc)[3]) {
+    const int n2 = a.n2, P = a.P, rs = a.rs, n0 = a.n0, n1 = a.n1;
+    // lv at the centre planes: with one row per thread a second queue holds it from the lead
+    // plane on; with more there are no registers for it (48^3, C = 3, 1024
+    // systems at omega 8.8: spilled, 163 ms against 48) and it is read again, a few planes later
+    // and so mostly from the caches
+    constexpr bool UQ = C == 1;
+    constexpr int NU = UQ ? 6 + Z : Z;
+    double U[NU][C];
+    const int PL = (n1 + 11 + C) * rs;
+    const bool per = a.periodic != 0;
+    constexpr int kWarm = C == 1 ? 6 : 3;    // planes of w loaded together
+    if (warm) {
+#pragma unroll
+        for (int s0 = 0; s0 < 12; s0 += kWarm) {
+            double t[kWarm][C];
+#pragma unroll
+            for (int s = 0; s < kWarm; ++s) {
+                int z = s0 + s - 6;
+                z += (z < 0) ? n2 : 0;
+#pragma unroll
+                for (int i = 0; i < C; ++i) t[s][i] = ld(lw + z * P, rw.col[i]);
+            }
+#pragma unroll
+            for (int s = 0; s < kWarm; ++s)
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    const double vo = Q[s0 + s][i];
+                    if (UQ && s0 + s >= 6) U[(s0 + s + 6) % 12 % NU][i] = vo;
+                    Q[s0 + s][i] = vnext(cw, t[s][i], cv, vo);
+                }
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 12; ++s) {
+            const int z = s - 6 + ((s < 6) ? n2 : 0);
+            double w[C], v[C];
+#pragma unroll
+            for (int i = 0; i < C; ++i) w[i] = v[i] = 0.0;
+            if (per || s >= 6) {                          // box: planes below 0 are zero
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    w[i] = ld(lw + z * P, rw.col[i]);
+                    v[i] = ld(lv + z * P, rw.col[i]);
+                    if (RAG && !per && !rw.own_[i]) w[i] = v[i] = 0.0;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                Q[s][i] = vnext(cw, w[i], cv, v[i]);
+                if (UQ && s >= 6) U[(s + 6) % 12 % NU][i] = v[i];
+            }
+            // one plane's loads at a time: a cold start is rare, its registers are not
+            asm volatile("" ::: "memory");
+        }
+    }
+    double LW[Z][C], LV[Z][C], PV[Z][C], UV[Z][C];
+    // lead planes zo + 6 + zz of the step at zo, and V_loc of its centre planes
+    auto fetch = [&](int zo) {
+#pragma unroll
+        for (int zz = 0; zz < Z; ++zz) {
+            const int zu = zo + 6 + zz;
+            if (zu < n2) {
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    LW[zz][i] = ld(lw + zu * P, rw.col[i]);
+                    LV[zz][i] = ld(lv + zu * P, rw.col[i]);
+                    if (RAG && !per && !rw.own_[i]) LW[zz][i] = LV[zz][i] = 0.0;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    LW[zz][i] = per ? ld(vout + (zu - n2) * P, rw.col[i]) : 0.0;
+                    LV[zz][i] = 0.0;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                PV[zz][i] = ld(a.vloc + (zo + zz) * P, rw.col[i]);
+                if constexpr (!UQ) UV[zz][i] = ld(lv + (zo + zz) * P, rw.col[i]);
+            }
+        }
+    };
+    fetch(0);
+    const int nsteps = n2 / Z;
+#pragma unroll 1
+    for (int stp = 0; stp < nsteps; ++stp) {
+        const int zo = stp * Z;
+        double VV[Z][C];
+#pragma unroll
+        for (int zz = 0; zz < Z; ++zz) {
+            const bool past = zo + 6 + zz >= n2;
+            const double c1 = past ? 1.0 : cw;
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                Q[12 + zz][i] = vnext(c1, LW[zz][i], cv, LV[zz][i]);
+                if constexpr (UQ) U[6 + zz][i] = LV[zz][i];
+                else U[zz][i] = UV[zz][i];
+                VV[zz][i] = PV[zz][i];
+            }
+        }
+        // ragged: the fetches past the top read v of rows that other threads stored
+        if (RAG && zo + Z + 6 <= n2 && zo + 2 * Z + 6 > n2) global_barrier();
+        if (stp + 1 < nsteps) fetch(zo + Z);
+        double* L = planes + (a.nbuf == 2 ? (stp & 1) : 0) * Z * PL;
+#pragma unroll
+        for (int zz = 0; zz < Z; ++zz)
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+                if (rw.template own<RAG>(i))
+                    cocg::stage_point(L + zz * PL, rs, n0, n1, rw.cx, rw.y0 + i, Q[6 + zz][i], per,
+                                      true);
+        lds_barrier();
+#pragma unroll
+        for (int zz = 0; zz < Z; ++zz) {
+            const double* Lc = L + zz * PL + cocg::lds_center(rs, rw.cx, rw.y0);
+            double s[C];
+#pragma unroll
+            for (int i = 0; i < C; ++i) s[i] = (diag0 + VV[zz][i]) * Q[6 + zz][i] - cp * U[zz][i];
+            // y: the rows above and below the thread's rows from LDS, its own from the queue
+#pragma unroll
+            for (int k = 1; k <= 6; ++k) {
+                const double b1 = Lc[-k * rs], b2 = Lc[(C - 1 + k) * rs];
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    if (k + i <= 6) s[i] += a.cw[k + i] * b1;
+                    if (k + C - 1 - i <= 6) s[i] += a.cw[k + C - 1 - i] * b2;
+                }
+                hold<C>(s);
+            }
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+#pragma unroll
+                for (int j = 0; j < C; ++j)
+                    if (i != j) s[i] += a.cw[i > j ? i - j : j - i] * Q[6 + zz][j];
+#pragma unroll
+            for (int k = 1; k <= 6; ++k) {
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    const double a1 = Lc[i * rs + k], a2 = Lc[i * rs - k];
+                    s[i] += a.cw[k] * ((a1 + a2) + (Q[6 + zz + k][i] + Q[6 + zz - k][i]));
+                }
+                hold<C>(s);
+            }
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                if (!rw.template own<RAG>(i)) continue;
+                const int off = (zo + zz) * P;
+                const double c = Q[6 + zz][i];
+                st(vout + off, rw.col[i], c);
+                st(wout + off, rw.col[i], s[i]);
+                acc[0] += c * s[i];
+                acc[1] += s[i] * s[i];
+                acc[2] += c * c;
+            }
+        }
+        if (a.nbuf == 1) lds_barrier();      // single buffer: reads done before the next write
+#pragma unroll
+        for (int s = 0; s < 12; ++s)
+#pragma unroll
+            for (int i = 0; i < C; ++i) Q[s][i] = Q[s + Z][i];
+        if constexpr (UQ) {
+#pragma unroll
+            for (int s = 0; s < 6; ++s)
+#pragma unroll
+                for (int i = 0; i < C; ++i) U[s][i] = U[s + Z][i];
+        }
+    }
+}
+
+// p <- v_j - l_j p, x <- x + e_j p (e = zeta / d) over the m newest basis vectors, in order: the
+// same operations on every point however many steps one update takes, so a solve's bits do not
+// depend on the ring.  The first update starts from x = 0, p = 0, and scales v_1, which is stored
+// as b, by s1 = 1 / |b|.  p is not stored at the end of a solve (done).
+struct Coef {
+    double lr, li, er, ei;
+};
+
+template <typename XS>
+__device__ __forceinline__ void update_px(int64_t nd, const double* ring, double2* p, XS* x,
+                                          const Coef* coef, int m, bool first, double s1,
+                                          bool done) {
+    constexpr bool CX = std::is_same<XS, double2>::value;
+    const unsigned n = unsigned(nd);
+    Coef c[kRing];
+#pragma unroll
+    for (int j = 0; j < kRing; ++j) c[j] = coef[j < m ? j : 0];
+    for (unsigned i = threadIdx.x; i < n; i += blockDim.x) {
+        double v[kRing];
+#pragma unroll
+        for (int j = 0; j < kRing; ++j)
+            if (j < m) v[j] = ld(ring + j * nd, i);
+        double2 pv{0.0, 0.0};
+        double xr = 0.0, xi = 0.0;
+        if (first) {
+            v[0] *= s1;
+        } else {
+            pv = ld(p, i);
+            if constexpr (CX) {
+                const double2 t = ld(x, i);
+                xr = t.x;
+                xi = t.y;
+            } else {
+                xr = ld(x, i);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kRing; ++j) {
+            if (j < m) {
+                const double pr = v[j] - c[j].lr * pv.x + c[j].li * pv.y;
+                pv.y = -c[j].lr * pv.y - c[j].li * pv.x;
+                pv.x = pr;
+                xr += c[j].er * pv.x - c[j].ei * pv.y;
+                if constexpr (CX) xi += c[j].er * pv.y + c[j].ei * pv.x;
+            }
+        }
+        if constexpr (CX) st(x, i, double2{xr, xi});
+        else st(x, i, xr);
+        if (!done) st(p, i, pv);
+    }
+}
+
+// RAG: C does not divide n1.
+template <typename XS, int C, int Z, int BSMAX, bool RAG>
+__global__ __attribute__((amdgpu_flat_work_group_size(64, BSMAX)))
+void rcocg_wg(Args a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double* red = reinterpret_cast<double*>(smem_raw);                 // 16 waves x 3
+    Coef* coef = reinterpret_cast<Coef*>(smem_raw + 16 * 3 * sizeof(double));
+    int* next = reinterpret_cast<int*>(coef + kRing);
+    double* planes = reinterpret_cast<double*>(coef + kRing) + 2;
+    const int tid = threadIdx.x, BS = blockDim.x;
+    Rows<C> rw;
+    {
+        const bool on = tid < (a.n1 + C - 1) / C * a.n0;
+        const int t = on ? tid : 0;
+        rw.on = on;
+        rw.cx = t % a.n0;
+        rw.y0 = t / a.n0 * C;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const int y = rw.y0 + i;
+            rw.own_[i] = on && y < a.n1;
+            rw.col[i] = unsigned((RAG && y >= a.n1 ? y - a.n1 : y) * a.n0 + rw.cx);
+        }
+    }
+    {   // ghost entries outside an isolated box read zero
+        const int nent = a.nbuf * Z * (a.n1 + 11 + C) * a.rs;
+        for (int e = tid; e < nent; e += BS) planes[e] = 0.0;
+    }
+    double* ring = a.pool + int64_t(blockIdx.x) * (a.ring + kSlotExtra) * a.nd;
+    double* w = ring + a.ring * a.nd;
+    double2* p = reinterpret_cast<double2*>(w + a.nd);
+    double Q[12 + Z][C];
+    for (;;) {
+        global_barrier();           // slot and LDS free for the next system
+        if (tid == 0) *next = atomicAdd(a.counter, 1);
+        lds_barrier();
+        const int pos = __builtin_amdgcn_readfirstlane(*next);
+        if (pos >= a.nsys) break;
+        const int sys = a.order[pos];
+        const double omega = a.omega_v[sys / a.ns];
+        const double diag = a.cw[0] - a.eps[sys % a.ns];
+        const double* b = a.rhs + int64_t(sys) * a.nd;
+        XS* x = reinterpret_cast<XS*>(a.x) + int64_t(sys) * a.nd;
+        double sigma = 0.0, delta = 0.0, beta = 0.0, sc = 1.0, tgt2 = 0.0;
+        double lr = 0.0, li = 0.0, zr = 0.0, zi = 0.0, ir = 0.0, ii = 0.0;   // l, zeta, 1/d
+        double ibeta = 1.0, bn = 0.0, ibn = 0.0;
+        int it = 0, stat = 0, slot = 0;               // slot = it mod ring
+        bool done = false, px_first = true, carry = false;
+        bool redo = false;
+        while (!done) {
+            const bool first = it == 0;
+            double* vnew = ring + slot * a.nd;
+            const double* vold = first ? b : ring + ((slot ? slot : a.ring) - 1) * a.nd;
+            // v_k = (w - delta v_{k-1}) / beta; v_1 stays unnormalised (sc = 1 / |b| carries its
+            // norm): the first sweep reads b itself.  A repeated sweep reads the stored v_k.
+            const bool plain = first || redo;
+            const double c1 = plain ? 1.0 : sc * ibeta;
+            const double c2 = plain ? 0.0 : -delta * sc * ibeta;
+            const double cp = first ? 0.0 : beta * sc;
+            double acc[3] = {0.0, 0.0, 0.0};
+            sweep<C, Z, RAG>(a, rw, planes, diag - sigma, redo ? vnew : (first ? b : w), vold, c1, c2,
+                        cp, vnew, w, Q, carry, acc);
+            if (RAG) global_barrier();           // w of rows that other threads stored
+            wg_reduce<3>(acc, red);
+            if (first) {
+                if (!(acc[2] > 0.0)) break;           // zero right-hand side
+                tgt2 = uniform(a.tol2 * acc[2]);
+                bn = uniform(sqrt(acc[2]));
+                ibn = uniform(1.0 / bn);
+                acc[0] = uniform(acc[0] / acc[2]);
+                acc[1] = uniform(acc[1] / acc[2]);
+            }
+            double b2 = uniform(acc[1] - acc[0] * acc[0]);
+            if (b2 < 1e-3 * acc[1] && !redo) {
+                // cancellation: once more with sigma = alpha
+                sigma = uniform(sigma + acc[0]);
+                carry = false;
+#pragma unroll
+                for (int q = 0; q < 12 + Z; ++q)
+#pragma unroll
+                    for (int i = 0; i < C; ++i) Q[q][i] = 0.0;
+                redo = true;
+                continue;
+            }
+            redo = false;
+            sc = first ? ibn : 1.0;
+            carry = a.periodic != 0;
+            const double alpha = sigma + acc[0];
+            delta = uniform(acc[0]);
+            b2 = b2 > 0.0 ? b2 : (b2 <= 0.0 ? 0.0 : b2);      // NaN stays
+            // factor step
+            lr = beta * ir;
+            li = beta * ii;
+            const double dr = alpha - beta * lr, di = -omega - beta * li;
+            if (first) {
+                zr = bn;
+                zi = 0.0;
+            } else {
+                const double t = -(lr * zr - li * zi);
+                zi = -(lr * zi + li * zr);
+                zr = t;
+            }
+            const double id2 = 1.0 / (dr * dr + di * di);
+            ir = uniform(dr * id2);
+            ii = uniform(-di * id2);
+            zr = uniform(zr);
+            zi = uniform(zi);
+            const double er = zr * ir - zi * ii, ei = zr * ii + zi * ir;   // zeta / d
+            if (tid == 0) coef[slot] = Coef{lr, li, er, ei};
+            beta = uniform(sqrt(b2));
+            ibeta = uniform(b2 > 0.0 ? 1.0 / sqrt(b2) : 0.0);
+            sigma = uniform(alpha);
+            const double res2 = b2 * (er * er + ei * ei);
+            ++it;
+            const int m = ++slot;                     // basis vectors not yet in x
+            if (slot == a.ring) slot = 0;
+            if (!(res2 >= 0.0) || !(res2 < INFINITY)) {
+                stat = 2;                              // not a number: reported as a breakdown
+                done = true;
+            } else if (res2 <= tgt2) {
+                done = true;
+            } else if (it >= a.max_iter) {
+                stat = 1;
+                done = true;
+            }
+            if (done || slot == 0) {
+                global_barrier();
+                update_px<XS>(a.nd, ring, p, x, coef, m, px_first, ibn, done);
+                px_first = false;
+                carry = false;              // the queue's registers are free for the update
+#pragma unroll
+                for (int q = 0; q < 12 + Z; ++q)
+#pragma unroll
+                    for (int i = 0; i < C; ++i) Q[q][i] = 0.0;
+                global_barrier();
+            }
+        }
+        if (it == 0) {
+            // zero right-hand side: x = 0 (not a number where b is not finite)
+            for (unsigned i = tid; i < unsigned(a.nd); i += BS) {
+                const double v = 0.0 * ld(b, i);
+                if constexpr (std::is_same<XS, double>::value) st(x, i, v);
+                else st(x, i, double2{v, 0.0});
+            }
+        }
+        if (tid == 0) {
+            a.iters[sys] = it;
+            a.status[sys] = stat;
+            if (a.refinements) a.refinements[sys] = 0;
+        }
+    }
+}
+
+}  // namespace rcocg
+}  // namespace rpa

@@ -621,6 +621,18 @@ hipError_t launch_to_float(int64_t n, const double* src, float* dst, hipStream_t
     return hipGetLastError();
 }
 
+__global__ void real_part_kernel(int64_t n, const double* __restrict__ src,
+                                 double* __restrict__ dst) {
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = src[2 * i];
+}
+
+hipError_t launch_real_part(int64_t n, const double* src, double* dst, hipStream_t s) {
+    hipLaunchKernelGGL(real_part_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, n, src,
+                       dst);
+    return hipGetLastError();
+}
+
 hipError_t launch_copy(int64_t n, const double* src, double* dst, hipStream_t s) {
     hipLaunchKernelGGL(copy_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, n, src, dst);
     return hipGetLastError();

@@ -1,0 +1,107 @@
+"""GPU parity of the real-form COCG kernel (real Lanczos basis, one sweep per iteration) against
+the oracle's complex COCG, at the edges of its launch shapes: the smallest grid, one, two and
+three rows per thread with and without a ragged last row group, odd and even n2, an isolated box,
+iteration caps around the ring of basis vectors, and launches of few and of many systems."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import chi0 as ochi0
+from paper_2504_01816_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-300))
+
+
+def make(shape, ns, seed, bc="periodic", h=0.45):
+    """A cell with random orthonormal orbitals and eigenvalues below the spectrum of H, which is
+    all that the solver sees of a ground state."""
+    rng = np.random.default_rng(seed)
+    nd = int(np.prod(shape))
+    q = np.linalg.qr(rng.standard_normal((nd, ns)))[0].T
+    vloc = rng.uniform(-1.0, 0.5, nd)
+    eps = np.sort(rng.uniform(-2.0, -1.2, ns))
+    return synth.Cell(shape, h, vloc, np.ascontiguousarray(q / np.sqrt(h ** 3)), eps, 0.0, 0.0,
+                      seed, bc=bc)
+
+
+def chi0(c, X, omega, tol, **opts):
+    out, rc, st = api.rpa_apply_chi0(api.device_cell(c, DEV), omega, torch.tensor(X, device=DEV),
+                                     dict(cocg_tol=tol, **opts))
+    return out.cpu().numpy(), rc, st
+
+
+# two FP64 solvers that meet a residual of 1e-12 differ by cond(A) 1e-12 <= 1e-9 here
+@pytest.mark.parametrize("shape,bc", [
+    ((7, 7, 12), "periodic"), ((7, 8, 13), "dirichlet"),
+    ((16, 16, 16), "periodic"), ((18, 17, 15), "dirichlet"), ((24, 23, 14), "periodic"),
+    ((32, 32, 12), "periodic"), ((33, 32, 12), "periodic"), ((35, 37, 13), "periodic"),
+    ((35, 37, 12), "dirichlet"), ((48, 45, 12), "periodic"), ((47, 46, 13), "periodic"),
+    ((46, 47, 12), "dirichlet"), ((52, 50, 12), "periodic")])
+def test_real_form_matches_oracle(shape, bc, capfd, monkeypatch):
+    say("real form", shape, bc)
+    monkeypatch.setenv("RPA_COCG_VERBOSE", "1")
+    c = make(shape, 2, 3, bc)
+    X = np.random.default_rng(4).standard_normal((2, c.nd))
+    for omega in (0.1, 2.0):
+        out, rc, st = chi0(c, X, omega, 1e-12)
+        ref, iters, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, omega, shape, c.h, 1e-12,
+                                         5000, bc=bc)
+        assert rc == 0 and rel(out.T, ref) < 1e-9, (omega, rel(out.T, ref))
+        assert abs(st["cocg_iters_total"] - int(iters.sum())) <= iters.size
+    # planes over 48 x 48 points stay on the complex kernel
+    assert ("rcocg shape" in capfd.readouterr().err) == (shape[0] * shape[1] <= 48 * 48)
+
+
+@pytest.mark.parametrize("cap", [1, 2, 3, 7, 8, 9, 16, 17])
+def test_real_form_iteration_caps(cap):
+    # the partial solution after `cap` steps, with a ring that is part full, full and just reused;
+    # rounding alone separates the two after this few steps
+    say("real form cap", cap)
+    c = make((12, 13, 14), 3, 5)
+    X = np.random.default_rng(6).standard_normal((2, c.nd))
+    out, rc, st = chi0(c, X, 0.5, 1e-14, cocg_max_iter=cap)
+    ref, _, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.5, c.shape, c.h, 1e-14, cap)
+    assert rc == 1 and st["cocg_iters_max"] == cap and st["n_unconverged"] == 6
+    assert rel(out.T, ref) < 1e-11
+
+
+def test_real_form_bits_do_not_depend_on_the_launch():
+    # few systems keep a short ring, many a long one, and slots serve one system after another:
+    # a column's bits are the same in every launch, and a zero column gives exactly zero
+    say("real form, launch independence")
+    c = make((14, 12, 13), 4, 7)
+    X = np.random.default_rng(8).standard_normal((600, c.nd))
+    X[5] = 0.0
+    many, rc, st = chi0(c, X, 0.3, 1e-10)
+    assert rc == 0 and st["cocg_systems"] == 2400 and np.all(many[5] == 0.0)
+    few, _, _ = chi0(c, X[3:7], 0.3, 1e-10)
+    assert np.array_equal(few, many[3:7])
+    mixed, _, _ = chi0(c, X[3:7], 0.1, 1e-10, precision=1)
+    fp64, _, _ = chi0(c, X[3:7], 0.1, 1e-10)
+    assert np.array_equal(mixed, fp64)
+
+
+def test_real_form_eigenvector_right_hand_sides():
+    # plane waves on a constant potential: every right-hand side is an eigenvector of A, so the
+    # first step converges and the sum of squares that gives beta cancels; a small second wave
+    # then needs exactly one more step
+    say("real form, eigenvectors")
+    shape = (12, 14, 16)
+    c = synth.uniform_cell(shape, 0.5, 0.3)
+    z, y, x = np.meshgrid(*(np.arange(n) for n in shape[::-1]), indexing="ij")
+    w1 = np.cos(2 * np.pi * x / 12).reshape(-1)
+    w2 = np.sin(2 * np.pi * (y / 14 + 2 * z / 16)).reshape(-1)
+    X = np.stack([w1, w2, w1 + 1e-5 * w2])
+    out, rc, st = chi0(c, X, 0.7, 1e-10)
+    ref, iters, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.7, shape, 0.5, 1e-10, 5000)
+    assert rc == 0 and st["cocg_iters_total"] == int(iters.sum())
+    assert rel(out.T, ref) < 1e-12
