@@ -411,7 +411,7 @@ void carve_sub(Carver& cv, const Grid& g, int ns, int nr, const Opts& o, SubBuf&
     b.ework = cv.take<double>(2 * sq);
     b.escal = cv.take<double>(8);
     b.eigw = cv.take<double>(nr);
-    b.eigwork = cv.take<double>(2 * sq);
+    b.eigwork = cv.take<double>(2 * sq + 8 * size_t(nr));
     b.info = cv.take<int>(8);
 }
 
@@ -471,21 +471,15 @@ void carve_back(Carver& cv, const Grid& g, int ns, int nr, const Opts& o, BackBu
     b.U = cv.take<double>(blk);
     b.Y = cv.take<double>(sq);
     b.mu = cv.take<double>(nr);
-    b.eigwork = cv.take<double>(2 * sq);
+    b.eigwork = cv.take<double>(2 * sq + 8 * size_t(nr));
     b.coefk = cv.take<double>(nr);
 }
 
 // ------------------------------------------------------------------ building blocks
 int coulomb_setup(const Grid& g, const CoulombBuf& b, hipStream_t s) {
-    if (g.periodic()) {
-        RPA_HIP(launch_eigbasis_1d(g.n0, g.h, b.Ux, b.kx, s));
-        RPA_HIP(launch_eigbasis_1d(g.n1, g.h, b.Uy, b.ky, s));
-        RPA_HIP(launch_eigbasis_1d(g.n2, g.h, b.Uz, b.kz, s));
-    } else {
-        RPA_HIP(launch_eigbasis_1d_box(g.n0, g.h, b.Ux, b.kx, b.ework, s));
-        RPA_HIP(launch_eigbasis_1d_box(g.n1, g.h, b.Uy, b.ky, b.ework, s));
-        RPA_HIP(launch_eigbasis_1d_box(g.n2, g.h, b.Uz, b.kz, b.ework, s));
-    }
+    double* const U[3] = {b.Ux, b.Uy, b.Uz};
+    double* const k[3] = {b.kx, b.ky, b.kz};
+    RPA_HIP(launch_eigbases(g, U, k, b.ework, s));
     return RPA_OK;
 }
 
@@ -819,15 +813,9 @@ int solve_chunk(const rpa_cell* cell, const Grid& g, const Opts& o, const Chi0Bu
 int precond_setup(const rpa_cell* cell, const Grid& g, const Chi0Buf& b, Chi0Host& h,
                   hipStream_t s) {
     if (!b.precond) return RPA_OK;
-    if (g.periodic()) {
-        RPA_HIP(launch_eigbasis_1d(g.n0, g.h, b.Ux, b.kx, s));
-        RPA_HIP(launch_eigbasis_1d(g.n1, g.h, b.Uy, b.ky, s));
-        RPA_HIP(launch_eigbasis_1d(g.n2, g.h, b.Uz, b.kz, s));
-    } else {
-        RPA_HIP(launch_eigbasis_1d_box(g.n0, g.h, b.Ux, b.kx, b.bwork, s));
-        RPA_HIP(launch_eigbasis_1d_box(g.n1, g.h, b.Uy, b.ky, b.bwork, s));
-        RPA_HIP(launch_eigbasis_1d_box(g.n2, g.h, b.Uz, b.kz, b.bwork, s));
-    }
+    double* const U[3] = {b.Ux, b.Uy, b.Uz};
+    double* const k[3] = {b.kx, b.ky, b.kz};
+    RPA_HIP(launch_eigbases(g, U, k, b.bwork, s));
     RPA_HIP(launch_vloc_mean(g.nd(), cell->v_loc, b.vmean, s));
     RPA_HIP(hipMemcpyAsync(&h.vmean, b.vmean, sizeof(double), hipMemcpyDeviceToHost, s));
     RPA_HIP(hipStreamSynchronize(s));

@@ -308,8 +308,19 @@ struct W7 {
     double w[7];
 };
 
-__global__ void eigbasis_kernel(int n, double h, W7 wt, double* U, double* kappa) {
+// Axis blockIdx.y; one workgroup per mode.
+struct Axes {
+    int n[3];
+    double* U[3];
+    double* kappa[3];
+};
+
+__global__ void eigbasis_kernel(Axes ax, double h, W7 wt) {
     const double* w = wt.w;
+    const int n = ax.n[blockIdx.y];
+    double* U = ax.U[blockIdx.y];
+    double* kappa = ax.kappa[blockIdx.y];
+    if (int(blockIdx.x) >= n) return;
     // Real Fourier basis of the periodic circulant -D2: column 0 constant, then cos/sin
     // pairs, and for even n the alternating mode.  kappa(theta) = h^-2 (-w0 - 2 sum w_p cos p theta).
     const int a = blockIdx.x;      // mode (column)
@@ -479,14 +490,6 @@ hipError_t launch_gemm_tall_small(int64_t nd, int m, const double* A, const doub
     return run_gemm(m, int(nd), m, 1, 0, SmallT{T, m}, TallKN{A, nd}, StoreColMajor{Y, nd}, s);
 }
 
-hipError_t launch_eigbasis_1d(int n, double h, double* U, double* kappa, hipStream_t s) {
-    W7 wt;
-    fd_weights(wt.w);
-    hipLaunchKernelGGL(eigbasis_kernel, dim3(n), dim3((n + 63) / 64 * 64), 0, s, n, h, wt, U,
-                       kappa);
-    return hipGetLastError();
-}
-
 // A = -D2 of an isolated box: A[i + n j] = -w_|i-j| / h^2 for |i - j| <= 6 (reaches beyond the
 // walls dropped)
 __global__ void box_matrix_kernel(int n, double h, W7 wt, double* A) {
@@ -496,7 +499,7 @@ __global__ void box_matrix_kernel(int n, double h, W7 wt, double* A) {
     A[i + int64_t(n) * j] = (d <= 6) ? -wt.w[d] / (h * h) : 0.0;
 }
 
-hipError_t launch_eigbasis_1d_box(int n, double h, double* U, double* kappa, double* work,
+static hipError_t eigbasis_1d_box(int n, double h, double* U, double* kappa, double* work,
                                   hipStream_t s) {
     W7 wt;
     fd_weights(wt.w);
@@ -505,6 +508,29 @@ hipError_t launch_eigbasis_1d_box(int n, double h, double* U, double* kappa, dou
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_syevj(n, A, work + int64_t(n) * n, kappa, U, s);
+}
+
+hipError_t launch_eigbases(const Grid& g, double* const U[3], double* const kappa[3],
+                           double* work, hipStream_t s) {
+    const int n[3] = {g.n0, g.n1, g.n2};
+    if (!g.periodic()) {
+        bool done = false;
+        hipError_t e = launch_box_basis(n, g.h, U, kappa, s, &done);
+        for (int a = 0; a < 3 && e == hipSuccess && !done; ++a)
+            e = eigbasis_1d_box(n[a], g.h, U[a], kappa[a], work, s);
+        return e;
+    }
+    Axes ax;
+    for (int a = 0; a < 3; ++a) {
+        ax.n[a] = n[a];
+        ax.U[a] = U[a];
+        ax.kappa[a] = kappa[a];
+    }
+    const int nm = std::max(n[0], std::max(n[1], n[2]));
+    W7 wt;
+    fd_weights(wt.w);
+    hipLaunchKernelGGL(eigbasis_kernel, dim3(nm, 3), dim3((nm + 63) / 64 * 64), 0, s, ax, g.h, wt);
+    return hipGetLastError();
 }
 
 static hipError_t kron_chunk(const Grid& g, int power, int nvec, const double* in, double* out,

@@ -65,12 +65,15 @@ void fd_weights(double w[7]);
 // ------------------------------------------------------------------ kernel launchers
 // All launchers enqueue on `s` and return hipError_t of the launch.
 
-// Kronecker nu^{power/2}: 1D eigenbases (basis[3] device, n_a*n_a each, kappa[3] device n_a)
-hipError_t launch_eigbasis_1d(int n, double h, double* U, double* kappa, hipStream_t s);
-// Isolated box: eigenpairs of the Dirichlet -D2 (banded Toeplitz of the weights, n <= 4096
-// not required small but work >= 3 n^2 doubles), kappa ascending, U[t + n a] = mode a.
-hipError_t launch_eigbasis_1d_box(int n, double h, double* U, double* kappa, double* work,
-                                  hipStream_t s);
+// 1D eigenbases of -D2 along the three axes (U[a]: n_a x n_a, U[t + n b] = mode b; kappa[a]:
+// n_a).  Periodic: the real Fourier basis, the constant first.  Isolated box: Dirichlet; work
+// holds 3 n^2 doubles of the longest axis.
+hipError_t launch_eigbases(const Grid& g, double* const U[3], double* const kappa[3],
+                           double* work, hipStream_t s);
+// Isolated box, all axes in one launch where they fit LDS (*done says whether they did).
+hipError_t launch_box_basis(const int n[3], double h, double* const U[3], double* const kappa[3],
+                            hipStream_t s, bool* done);
+// Kronecker nu^{power/2}
 hipError_t launch_kron_apply(const Grid& g, int power, int nvec, const double* in, double* out,
                              double* tmp, const double* Ux, const double* Uy, const double* Uz,
                              const double* kx, const double* ky, const double* kz,
@@ -232,7 +235,8 @@ hipError_t launch_energy_logdet(int m, const double* C, double scale, double* wo
 hipError_t launch_sq_energy(int m, const double* C, int n_o, double scale, double* work,
                             double* out, int* info, hipStream_t s);
 // Symmetric eigen-decomposition by cyclic Jacobi: A (m x m) copied to work; eigenvalues
-// ascending into w, eigenvectors (columns) into Y if Y != nullptr.
+// Symmetric A (m x m): eigenvalues ascending into w, eigenvectors (columns) into Y if not null;
+// work: 2 m^2 + 6 m + 4 doubles.
 hipError_t launch_syevj(int m, const double* A, double* work, double* w, double* Y,
                         hipStream_t s);
 
