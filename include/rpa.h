@@ -61,7 +61,9 @@ extern "C" {
 
 /* ---------------------------------------------------------------- option values */
 #define RPA_FP64          0   /* every step in float64 / complex128 */
-#define RPA_MIXED         1   /* COCG state in complex64 with float64 residual refinement */
+#define RPA_MIXED         1   /* the faster of FP64 solves with a float64 residual check and COCG
+                                 state in complex64 with float64 residual refinement; either way
+                                 the tolerance holds for the exact residual */
 
 #define RPA_WARM          0   /* Sec. 3: the subspace of one frequency starts the next */
 #define RPA_INDEPENDENT   1   /* every frequency starts from V0; all frequencies still
@@ -134,10 +136,12 @@ typedef struct rpa_options {
                                 the state is that of RPA_FLAG_PRECOND (112 B per point and
                                 system). */
     double mixed_min_omega;  /* RPA_MIXED: trial vectors at frequencies below this (Ha) are
-                                solved in FP64 (complex128 state) instead of complex64: near the
-                                real axis the shifts approach the spectrum and the complex64
-                                recurrences need more extra iterations than they save; 0 runs
-                                every frequency in complex64.  Default 0.2. */
+                                solved as in RPA_FP64: near the real axis the shifts approach the
+                                spectrum and complex64 recurrences need more extra iterations
+                                than they save.  At and above it, grids whose x-y plane has at
+                                most 2304 points are solved in FP64 and the exact residual is
+                                tested (faster than complex64 there), larger planes in complex64;
+                                0 runs every frequency in complex64.  Default 0.2. */
 } rpa_options;
 
 /* Counters accumulated by a call (added to the struct's current contents). */
@@ -154,8 +158,9 @@ typedef struct rpa_stats {
     double cocg_kernel_ms;        /* their summed duration, from HIP events recorded on the
                                      stream of each launch */
     double cocg_point_iters;      /* sum over systems of (COCG iterations x N_d) */
-    int32_t fp64_fallbacks;       /* RPA_MIXED: systems that reached cocg_max_iter or broke
-                                     down in complex64 and were solved on in FP64 from where
+    int32_t fp64_fallbacks;       /* RPA_MIXED: systems that reached cocg_max_iter, broke down
+                                     or missed the tolerance by their exact residual
+                                     and were solved on in FP64 from where
                                      they stopped, with the exact residual (up to
                                      cocg_max_iter further iterations); only a second cap or
                                      breakdown there counts in n_unconverged / n_breakdown */

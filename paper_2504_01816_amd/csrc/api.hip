@@ -323,24 +323,21 @@ void carve_chi0(Carver& cv, const Grid& g, int ns, int nvec, const Opts& o, bool
     b.pa = cv.take<char>(size_t(S) * nd * cplx);
     b.pb = cv.take<char>(size_t(S) * nd * cplx);
     b.xlo = b.mixed ? cv.take<char>(size_t(S) * nd * 8) : nullptr;
-    // Real-form COCG keeps its right-hand sides in r (mixed buffers: in r_hi) and its pool of
-    // slots behind them, up to the end of the direction vectors; launches of few systems get
-    // the rest of their slots here.
+    // Real-form COCG keeps its right-hand sides in the first 8 B per point and system of r and
+    // its pool of slots behind them, up to the end of the direction vectors; launches of few
+    // systems get the rest of their slots here.
     b.real_form = !b.precond && rcocg_fits(g);
-    b.rhs = nullptr;
+    b.rhs = static_cast<double*>(b.r);
     b.pool = nullptr;
     b.pool_bytes = 0;
     if (b.real_form) {
-        const size_t skip = b.mixed ? 0 : (size_t(S) * nd * 8 + 255) / 256 * 256;
-        const size_t start = cv.used - size_t(S) * nd * (b.mixed ? 32 : 48) + skip;
-        b.pool_bytes = rcocg_pool_bytes(g, S) + 512;   // 512: see the restart of broken-down systems
-        const size_t first = start / 256 * 256 + 256;
+        const size_t first = (cv.used - size_t(S) * nd * (b.mixed ? 24 : 40)) / 256 * 256 + 256;
+        b.pool_bytes = rcocg_pool_bytes(g, S);
         if (first + b.pool_bytes > cv.used) cv.take<char>(first + b.pool_bytes - cv.used);
         if (cv.base) b.pool = reinterpret_cast<double*>(cv.base + first);
     }
     b.x = cv.take<char>(size_t(S) * nd * (b.x_complex ? 16 : 8));
     b.rhi = b.mixed ? cv.take<double>(2 * size_t(S) * nd) : nullptr;
-    if (b.real_form) b.rhs = b.mixed ? b.rhi : static_cast<double*>(b.r);
     b.b2 = b.mixed ? cv.take<double>(S) : nullptr;
     b.vloc32 = b.mixed ? cv.take<float>(size_t(nd)) : nullptr;
     b.iters = cv.take<int>(S);
@@ -657,6 +654,15 @@ RcocgLaunch real_launch(const rpa_cell* cell, const Grid& g, const Opts& o, cons
     return R;
 }
 
+// RPA_MIXED at and above mixed_min_omega: where the real-form FP64 kernel has a launch shape it
+// solves faster than the complex64 one (48^3, omega 49.4, 16384 systems: 1.2 us per
+// system-iteration against 2.1) and takes the place of the complex64 recurrences; their float64
+// refinement stays as one float64 residual b - A x per system, on which the tolerance is tested.
+// mixed_min_omega = 0 asks for complex64 at every frequency.
+bool checked_real_form(const Chi0Buf& b, const Opts& o) {
+    return b.mixed && b.real_form && o.mixed_min_omega > 0.0 && !cocg_shape_forced();
+}
+
 // Solve the Sternheimer systems of the trial vectors j0 .. j0+nv-1 (columns of U, which
 // points at column j0), each at its own frequency h.omega[j].  With mixed buffers and
 // fp64_run, the run solves in FP64 inside the mixed state: the complex128 residual goes in
@@ -670,7 +676,8 @@ int solve_chunk(const rpa_cell* cell, const Grid& g, const Opts& o, const Chi0Bu
     const int64_t nd = g.nd();
     const double dV = g.h * g.h * g.h;
     RPA_HIP(launch_proj_coeff(nd, ns, nv, dV, cell->psi, U, b.part, b.nsplit, b.coeff, s));
-    const bool real_form = b.real_form && (!b.mixed || fp64_run) && !cocg_shape_forced();
+    const bool checked = !fp64_run && checked_real_form(b, o);
+    const bool real_form = b.real_form && (!b.mixed || fp64_run || checked) && !cocg_shape_forced();
     if (real_form) {
         RPA_HIP(launch_proj_rhs_real(nd, ns, nv, cell->psi, U, b.coeff, b.rhs, s));
     } else if (b.mixed && fp64_run) {
@@ -752,11 +759,12 @@ int solve_chunk(const rpa_cell* cell, const Grid& g, const Opts& o, const Chi0Bu
                            hipMemcpyHostToDevice, s));
     if (real_form) {
         RcocgLaunch R = real_launch(cell, g, o, b, ns * nv);
-        R.x_complex = x_complex;
+        R.x_complex = x_complex || checked;
         hipEvent_t e0, e1;
         RPA_CHECK(timer_events(&e0, &e1));
         RPA_HIP(hipEventRecord(e0, s));
         RPA_HIP(launch_rcocg(R, s));
+        if (checked) RPA_HIP(launch_residual_check(R, b.b2, s));
         RPA_HIP(hipEventRecord(e1, s));
         return RPA_OK;
     }
@@ -822,8 +830,9 @@ int precond_setup(const rpa_cell* cell, const Grid& g, const Chi0Buf& b, Chi0Hos
     return RPA_OK;
 }
 
-// Mixed precision: the systems of a chunk that stopped at the iteration cap or at a breakdown
-// of the complex64 recurrence (it can lose conjugacy on the most ill-conditioned shifts) are
+// Mixed precision: the systems of a chunk that stopped at the iteration cap, at a breakdown of
+// the complex64 recurrence (it can lose conjugacy on the most ill-conditioned shifts) or with an
+// exact residual above the tolerance (real form) are
 // solved on in FP64 from where they stopped, once (the restart of a broken-down COCG from its
 // current iterate and true residual): the mixed kernel leaves x_hi and the exact
 // r_hi = b - A x_hi, and the FP64 kernel solves A e = r_hi into x_hi += e to |r| <= tol |b|,
@@ -837,10 +846,11 @@ int continue_capped(const rpa_cell* cell, const Grid& g, const Opts& o, const Ch
     // systems that broke down at their first step have x_hi = 0 and r_hi = b: with a real-form
     // launch shape they are solved afresh, as in the FP64 path
     std::vector<int> capped, fresh;
+    const bool checked = checked_real_form(b, o);
     const bool real_form = b.real_form && !cocg_shape_forced();
     for (int i = 0; i < S; ++i) {
         if (h.st[i] != 1 && h.st[i] != 2) continue;
-        (real_form && h.st[i] == 2 && h.it[i] == 1 ? fresh : capped).push_back(i);
+        (real_form && !checked && h.st[i] == 2 && h.it[i] == 1 ? fresh : capped).push_back(i);
     }
     for (int pass = 0; pass < 2; ++pass) {
         std::vector<int>& list = pass == 0 ? fresh : capped;
@@ -853,19 +863,16 @@ int continue_capped(const rpa_cell* cell, const Grid& g, const Opts& o, const Ch
         hipEvent_t e0, e1;
         RPA_CHECK(timer_events(&e0, &e1));
         if (pass == 0) {
-            // right-hand sides packed over r, the pool behind them
-            const int64_t tot = int64_t(S) * g.nd();
-            RPA_HIP(launch_real_part(tot, b.rhi, static_cast<double*>(b.r), s));
-            const size_t skip = (size_t(tot) * sizeof(double) + 511) / 256 * 256;
+            RPA_HIP(launch_real_part(int64_t(S) * g.nd(), b.rhi, b.rhs, s));
             RcocgLaunch R = real_launch(cell, g, o, b, n);
-            R.rhs = static_cast<const double*>(b.r);
             R.x_complex = true;
-            R.pool += skip / sizeof(double);
-            R.pool_bytes -= skip;
             R.refinements = nullptr;
             RPA_HIP(hipEventRecord(e0, s));
             RPA_HIP(launch_rcocg(R, s));
         } else {
+            // the complex64 kernel ends with r_hi = b - A x_hi, the real form with x alone
+            if (checked)
+                RPA_HIP(launch_residual(real_launch(cell, g, o, b, n), b.rhi, s));
             CocgLaunch L{};
             L.g = g;
             L.nsys = n;

@@ -18,16 +18,18 @@ namespace rpa {
 namespace {
 
 using KernelFn = void (*)(rcocg::Args);
+using CheckFn = void (*)(rcocg::CheckArgs);
 
 struct Variant {
     int C, Z, bsmax;
     bool ragged;           // C does not divide n1
     KernelFn real, cplx;
+    CheckFn check;
 };
 
 #define RPA_V(CC, ZZ, BM, RG)                                        \
     {CC, ZZ, BM, RG, rcocg::rcocg_wg<double, CC, ZZ, BM, RG>,        \
-     rcocg::rcocg_wg<double2, CC, ZZ, BM, RG>}
+     rcocg::rcocg_wg<double2, CC, ZZ, BM, RG>, rcocg::check_wg<CC, BM, RG>}
 const Variant kTable[] = {
     RPA_V(1, 1, 256, false), RPA_V(1, 1, 512, false),  RPA_V(1, 1, 768, false), RPA_V(1, 1, 1024, false),
     RPA_V(1, 2, 256, false), RPA_V(1, 2, 512, false),  RPA_V(1, 2, 768, false), RPA_V(1, 2, 1024, false),
@@ -41,6 +43,14 @@ struct Shape {
     size_t lds = 0;
 };
 
+void stencil_weights(double h, double cw[7]) {
+    double w[7];
+    fd_weights(w);
+    const double ih2 = 1.0 / (h * h);
+    cw[0] = -0.5 * 3.0 * w[0] * ih2;
+    for (int k = 1; k <= 6; ++k) cw[k] = -0.5 * w[k] * ih2;
+}
+
 size_t lds_bytes(const Grid& g, int C, int Z, int nbuf, int rs) {
     return 16 * 3 * sizeof(double) + rcocg::kRing * sizeof(rcocg::Coef) + 16 +
            size_t(nbuf) * Z * (g.n1 + 11 + C) * rs * sizeof(double);
@@ -48,7 +58,8 @@ size_t lds_bytes(const Grid& g, int C, int Z, int nbuf, int rs) {
 
 Shape choose(const Grid& g) {
     int fC = 0, fZ = 0;
-    if (const char* e = std::getenv("RPA_RCOCG_SHAPE")) std::sscanf(e, "%d,%d", &fC, &fZ);
+    if (const char* e = std::getenv("RPA_RCOCG_SHAPE"))
+        if (std::sscanf(e, "%d,%d", &fC, &fZ) < 2) fC = fZ = 0;
     Shape best;
     double best_cost = 1e30;
     for (const Variant& v : kTable) {
@@ -103,11 +114,7 @@ hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
     a.n1 = L.g.n1;
     a.n2 = L.g.n2;
     a.P = L.g.n0 * L.g.n1;
-    double w[7];
-    fd_weights(w);
-    const double ih2 = 1.0 / (L.g.h * L.g.h);
-    a.cw[0] = -0.5 * 3.0 * w[0] * ih2;
-    for (int k = 1; k <= 6; ++k) a.cw[k] = -0.5 * w[k] * ih2;
+    stencil_weights(L.g.h, a.cw);
     a.vloc = L.vloc;
     a.eps = L.eps;
     a.ns = L.ns;
@@ -140,6 +147,56 @@ hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn, dim3(grid), dim3(s.bs), s.lds, st, a);
     return hipGetLastError();
+}
+
+namespace {
+
+hipError_t launch_check(const RcocgLaunch& L, const int* order, double* r, double* b2,
+                        hipStream_t st) {
+    const Shape s = choose(L.g);
+    if (!s.v) return hipErrorInvalidConfiguration;
+    rcocg::CheckArgs a{};
+    a.n0 = L.g.n0;
+    a.n1 = L.g.n1;
+    a.n2 = L.g.n2;
+    a.P = L.g.n0 * L.g.n1;
+    stencil_weights(L.g.h, a.cw);
+    a.vloc = L.vloc;
+    a.eps = L.eps;
+    a.omega_v = L.omega_v;
+    a.rhs = L.rhs;
+    a.ns = L.ns;
+    a.order = order;
+    a.x = static_cast<const double2*>(L.x);
+    a.rout = reinterpret_cast<double2*>(r);
+    a.tol2 = L.tol * L.tol;
+    a.nd = L.g.nd();
+    a.status = L.status;
+    a.refinements = L.refinements;
+    a.b2 = b2;
+    a.rs = s.rs;
+    a.nbuf = 2;
+    a.periodic = L.g.periodic() ? 1 : 0;
+    size_t lds = lds_bytes(L.g, s.v->C, 1, 2, s.rs);
+    if (lds > 150 * 1024) {
+        a.nbuf = 1;
+        lds = lds_bytes(L.g, s.v->C, 1, 1, s.rs);
+    }
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(s.v->check),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(s.v->check, dim3(L.nsys), dim3(s.bs), lds, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_residual(const RcocgLaunch& L, double* r, hipStream_t s) {
+    return launch_check(L, L.order, r, nullptr, s);
+}
+
+hipError_t launch_residual_check(const RcocgLaunch& L, double* b2, hipStream_t s) {
+    return launch_check(L, nullptr, nullptr, b2, s);
 }
 
 }  // namespace rpa

@@ -95,12 +95,61 @@ struct Rows {
     __device__ bool own(int i) const { return RAG ? own_[i] : on; }
 };
 
+template <int C, bool RAG>
+__device__ __forceinline__ Rows<C> make_rows(int n0, int n1) {
+    Rows<C> rw;
+    const int tid = threadIdx.x;
+    rw.on = tid < (n1 + C - 1) / C * n0;
+    const int t = rw.on ? tid : 0;
+    rw.cx = t % n0;
+    rw.y0 = t / n0 * C;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        const int y = rw.y0 + i;
+        rw.own_[i] = rw.on && y < n1;
+        rw.col[i] = unsigned((RAG && y >= n1 ? y - n1 : y) * n0 + rw.cx);
+    }
+    return rw;
+}
+
 // Ends a group of LDS reads: what was read is consumed here, which bounds the registers held by
 // reads in flight.
 template <int C>
 __device__ __forceinline__ void hold(double (&s)[C]) {
 #pragma unroll
     for (int i = 0; i < C; ++i) asm volatile("" : "+v"(s[i])::"memory");
+}
+
+// s[i] += the off-diagonal stencil of the thread's C rows: x and outer y neighbours from the LDS
+// plane (Lc: the first row's entry), z neighbours and the thread's own rows from the queue.
+template <int NQ, int C>
+__device__ __forceinline__ void stencil(const double (&cw)[7], const double* Lc, int rs,
+                                        const double (&Q)[NQ][C], int zc, double (&s)[C]) {
+    // y: the rows above and below the thread's rows from LDS, its own from the queue
+#pragma unroll
+    for (int k = 1; k <= 6; ++k) {
+        const double b1 = Lc[-k * rs], b2 = Lc[(C - 1 + k) * rs];
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if (k + i <= 6) s[i] += cw[k + i] * b1;
+            if (k + C - 1 - i <= 6) s[i] += cw[k + C - 1 - i] * b2;
+        }
+        hold<C>(s);
+    }
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+#pragma unroll
+        for (int j = 0; j < C; ++j)
+            if (i != j) s[i] += cw[i > j ? i - j : j - i] * Q[zc][j];
+#pragma unroll
+    for (int k = 1; k <= 6; ++k) {
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const double a1 = Lc[i * rs + k], a2 = Lc[i * rs - k];
+            s[i] += cw[k] * ((a1 + a2) + (Q[zc + k][i] + Q[zc - k][i]));
+        }
+        hold<C>(s);
+    }
 }
 
 // v_{k+1} at a point, with one rounding order wherever it is formed.
@@ -236,31 +285,7 @@ __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* 
             double s[C];
 #pragma unroll
             for (int i = 0; i < C; ++i) s[i] = (diag0 + VV[zz][i]) * Q[6 + zz][i] - cp * U[zz][i];
-            // y: the rows above and below the thread's rows from LDS, its own from the queue
-#pragma unroll
-            for (int k = 1; k <= 6; ++k) {
-                const double b1 = Lc[-k * rs], b2 = Lc[(C - 1 + k) * rs];
-#pragma unroll
-                for (int i = 0; i < C; ++i) {
-                    if (k + i <= 6) s[i] += a.cw[k + i] * b1;
-                    if (k + C - 1 - i <= 6) s[i] += a.cw[k + C - 1 - i] * b2;
-                }
-                hold<C>(s);
-            }
-#pragma unroll
-            for (int i = 0; i < C; ++i)
-#pragma unroll
-                for (int j = 0; j < C; ++j)
-                    if (i != j) s[i] += a.cw[i > j ? i - j : j - i] * Q[6 + zz][j];
-#pragma unroll
-            for (int k = 1; k <= 6; ++k) {
-#pragma unroll
-                for (int i = 0; i < C; ++i) {
-                    const double a1 = Lc[i * rs + k], a2 = Lc[i * rs - k];
-                    s[i] += a.cw[k] * ((a1 + a2) + (Q[6 + zz + k][i] + Q[6 + zz - k][i]));
-                }
-                hold<C>(s);
-            }
+            stencil<12 + Z, C>(a.cw, Lc, rs, Q, 6 + zz, s);
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 if (!rw.template own<RAG>(i)) continue;
@@ -295,15 +320,18 @@ struct Coef {
     double lr, li, er, ei;
 };
 
-template <typename XS>
+// REG: the coefficients in registers (else read from LDS at every point).
+template <typename XS, bool REG>
 __device__ __forceinline__ void update_px(int64_t nd, const double* ring, double2* p, XS* x,
                                           const Coef* coef, int m, bool first, double s1,
                                           bool done) {
     constexpr bool CX = std::is_same<XS, double2>::value;
     const unsigned n = unsigned(nd);
-    Coef c[kRing];
+    Coef cr[REG ? kRing : 1];
+    if constexpr (REG) {
 #pragma unroll
-    for (int j = 0; j < kRing; ++j) c[j] = coef[j < m ? j : 0];
+        for (int j = 0; j < kRing; ++j) cr[j] = coef[j < m ? j : 0];
+    }
     for (unsigned i = threadIdx.x; i < n; i += blockDim.x) {
         double v[kRing];
 #pragma unroll
@@ -326,11 +354,13 @@ __device__ __forceinline__ void update_px(int64_t nd, const double* ring, double
 #pragma unroll
         for (int j = 0; j < kRing; ++j) {
             if (j < m) {
-                const double pr = v[j] - c[j].lr * pv.x + c[j].li * pv.y;
-                pv.y = -c[j].lr * pv.y - c[j].li * pv.x;
+                if constexpr (!REG) asm volatile("" ::: "memory");
+                const Coef c = REG ? cr[REG ? j : 0] : coef[j];
+                const double pr = v[j] - c.lr * pv.x + c.li * pv.y;
+                pv.y = -c.lr * pv.y - c.li * pv.x;
                 pv.x = pr;
-                xr += c[j].er * pv.x - c[j].ei * pv.y;
-                if constexpr (CX) xi += c[j].er * pv.y + c[j].ei * pv.x;
+                xr += c.er * pv.x - c.ei * pv.y;
+                if constexpr (CX) xi += c.er * pv.y + c.ei * pv.x;
             }
         }
         if constexpr (CX) st(x, i, double2{xr, xi});
@@ -349,20 +379,7 @@ void rcocg_wg(Args a) {
     int* next = reinterpret_cast<int*>(coef + kRing);
     double* planes = reinterpret_cast<double*>(coef + kRing) + 2;
     const int tid = threadIdx.x, BS = blockDim.x;
-    Rows<C> rw;
-    {
-        const bool on = tid < (a.n1 + C - 1) / C * a.n0;
-        const int t = on ? tid : 0;
-        rw.on = on;
-        rw.cx = t % a.n0;
-        rw.y0 = t / a.n0 * C;
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-            const int y = rw.y0 + i;
-            rw.own_[i] = on && y < a.n1;
-            rw.col[i] = unsigned((RAG && y >= a.n1 ? y - a.n1 : y) * a.n0 + rw.cx);
-        }
-    }
+    const Rows<C> rw = make_rows<C, RAG>(a.n0, a.n1);
     {   // ghost entries outside an isolated box read zero
         const int nent = a.nbuf * Z * (a.n1 + 11 + C) * a.rs;
         for (int e = tid; e < nent; e += BS) planes[e] = 0.0;
@@ -466,7 +483,7 @@ void rcocg_wg(Args a) {
             }
             if (done || slot == 0) {
                 global_barrier();
-                update_px<XS>(a.nd, ring, p, x, coef, m, px_first, ibn, done);
+                update_px<XS, true>(a.nd, ring, p, x, coef, m, px_first, ibn, done);
                 px_first = false;
                 carry = false;              // the queue's registers are free for the update
 #pragma unroll
@@ -489,6 +506,110 @@ void rcocg_wg(Args a) {
             a.status[sys] = stat;
             if (a.refinements) a.refinements[sys] = 0;
         }
+    }
+}
+
+// ---------------------------------------------------------------- exact residual
+// r = b - (H - eps_n - i omega) x of a finished solve with complex solutions, in float64, one
+// system per workgroup: the real and the imaginary part of x are marched one after the other on
+// the solver's planes (the second finds x in the caches).  Norms mode (rout null): status 0
+// becomes 1 where |r| > tol |b|, refinements is 1, b2 = |b|^2.  Else r is stored, interleaved.
+// 48^3, 16384 systems: 23 ms beside 385 for the shortest solves (21 iterations); plain gathers of
+// the 37 points took 60.
+struct CheckArgs {
+    int n0, n1, n2, P;
+    double cw[7];
+    const double *vloc, *eps, *omega_v, *rhs;
+    int ns;
+    const int* order;      // null: system = block
+    const double2* x;
+    double2* rout;
+    double tol2;
+    int64_t nd;
+    int *status, *refinements;
+    double* b2;
+    int nbuf, rs, periodic;
+};
+
+template <int C, int BSMAX, bool RAG>
+__global__ __attribute__((amdgpu_flat_work_group_size(64, BSMAX))) void check_wg(CheckArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double* red = reinterpret_cast<double*>(smem_raw);                 // 16 waves x 3
+    double* planes = red + 48;
+    const int sys = a.order ? a.order[blockIdx.x] : int(blockIdx.x);
+    const int n0 = a.n0, n1 = a.n1, n2 = a.n2, P = a.P, rs = a.rs;
+    const int PL = (n1 + 11 + C) * rs;
+    const bool per = a.periodic != 0;
+    const double om = a.omega_v[sys / a.ns], diag = a.cw[0] - a.eps[sys % a.ns];
+    const double* x = reinterpret_cast<const double*>(a.x + int64_t(sys) * a.nd);
+    const double* b = a.rhs + int64_t(sys) * a.nd;
+    double* rout = a.rout ? reinterpret_cast<double*>(a.rout + int64_t(sys) * a.nd) : nullptr;
+    const Rows<C> rw = make_rows<C, RAG>(n0, n1);
+    for (int e = threadIdx.x; e < a.nbuf * PL; e += blockDim.x) planes[e] = 0.0;
+    double acc[3] = {0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int part = 0; part < 2; ++part) {
+        lds_barrier();
+        const double* xp = x + part;                 // the marched part, stride 2
+        const double* xo = x + 1 - part;             // the other one
+        const double so = part == 0 ? om : -om;
+        double Q[13][C];
+#pragma unroll
+        for (int s = 0; s < 13; ++s) {
+            const int zu = s - 6, z = zu < 0 ? zu + n2 : zu;
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                Q[s][i] = 0.0;
+                if (per || zu >= 0) Q[s][i] = ld(xp + 2 * z * P, 2 * rw.col[i]);
+                if (RAG && !per && !rw.own_[i]) Q[s][i] = 0.0;
+            }
+        }
+#pragma unroll 1
+        for (int z = 0; z < n2; ++z) {
+            double nx[C], V[C], xc[C], bv[C];
+            const int zn = z + 7;
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                nx[i] = 0.0;
+                if (per || zn < n2) nx[i] = ld(xp + 2 * (zn < n2 ? zn : zn - n2) * P, 2 * rw.col[i]);
+                if (RAG && !per && !rw.own_[i]) nx[i] = 0.0;
+                V[i] = ld(a.vloc + z * P, rw.col[i]);
+                xc[i] = ld(xo + 2 * z * P, 2 * rw.col[i]);
+                bv[i] = part == 0 ? ld(b + z * P, rw.col[i]) : 0.0;
+            }
+            double* L = planes + (a.nbuf == 2 ? (z & 1) : 0) * PL;
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+                if (rw.template own<RAG>(i))
+                    cocg::stage_point(L, rs, n0, n1, rw.cx, rw.y0 + i, Q[6][i], per, true);
+            lds_barrier();
+            double s[C];
+#pragma unroll
+            for (int i = 0; i < C; ++i) s[i] = (diag + V[i]) * Q[6][i] + so * xc[i];
+            stencil<13, C>(a.cw, L + cocg::lds_center(rs, rw.cx, rw.y0), rs, Q, 6, s);
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                if (!rw.template own<RAG>(i)) continue;
+                const double r = bv[i] - s[i];
+                acc[0] += r * r;
+                acc[1] += bv[i] * bv[i];
+                if (rout) st(rout + part + 2 * z * P, 2 * rw.col[i], r);
+            }
+            if (a.nbuf == 1) lds_barrier();
+#pragma unroll
+            for (int q = 0; q < 12; ++q)
+#pragma unroll
+                for (int i = 0; i < C; ++i) Q[q][i] = Q[q + 1][i];
+#pragma unroll
+            for (int i = 0; i < C; ++i) Q[12][i] = nx[i];
+        }
+    }
+    if (rout) return;
+    wg_reduce<3>(acc, red);
+    if (threadIdx.x == 0) {
+        if (a.status[sys] == 0 && !(acc[0] <= a.tol2 * acc[1])) a.status[sys] = 1;
+        if (a.refinements) a.refinements[sys] = 1;
+        a.b2[sys] = acc[1];
     }
 }
 

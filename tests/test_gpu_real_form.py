@@ -105,3 +105,25 @@ def test_real_form_eigenvector_right_hand_sides():
     ref, iters, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.7, shape, 0.5, 1e-10, 5000)
     assert rc == 0 and st["cocg_iters_total"] == int(iters.sum())
     assert rel(out.T, ref) < 1e-12
+
+
+@pytest.mark.parametrize("shape,bc", [((12, 13, 14), "periodic"), ((12, 13, 14), "dirichlet"),
+                                      ((35, 37, 12), "dirichlet"), ((35, 37, 13), "periodic"),
+                                      ((48, 45, 12), "periodic")])
+def test_mixed_real_form_is_checked_and_continued(shape, bc):
+    # the mixed path at omega >= mixed_min_omega: one exact residual per system; with a cap below
+    # what the solves need, every system goes on in FP64 from x and that residual
+    say("mixed, real form with the exact residual", shape, bc)
+    c = make(shape, 2, 9, bc)
+    X = np.random.default_rng(10).standard_normal((2, c.nd))
+    ref, iters, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.5, shape, c.h, 1e-10, 5000,
+                                     bc=bc)
+    out, rc, st = chi0(c, X, 0.5, 1e-10, precision=1)
+    assert rc == 0 and st["refinements"] == 4 and st["n_unconverged"] == 0
+    # the residual is met by both, so they differ by at most 2 cond(A) 1e-10
+    assert rel(out.T, ref) < 1e-8
+    cap = int(0.7 * iters.min())
+    out, rc, st = chi0(c, X, 0.5, 1e-10, precision=1, cocg_max_iter=cap)
+    assert rc == 0 and st["fp64_fallbacks"] == 4 and st["n_unconverged"] == 0
+    assert rel(out.T, ref) < 1e-8
+
