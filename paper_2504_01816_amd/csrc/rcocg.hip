@@ -1,17 +1,19 @@
-// Launch-shape selection for the real-form COCG kernel (design in rcocg_kernel.h).
+// Launch-shape selection for the real-form COCG kernels (design in rcocg_kernel.h and
+// rres_kernel.h).
 //
-// A shape is (C rows per thread, Z planes per barrier step).  One row per thread up to 1024
+// Grids whose columns and plane fit the registers of one workgroup take a resident kernel
+// (choose_resident).  Elsewhere the vectors stream, and a shape is (C rows per thread, Z planes per barrier step).  One row per thread up to 1024
 // columns: more rows share LDS reads, but the kernel waits on memory and wants waves (24^3: 26.5
 // ms with C = 1, 34 with 2, 47 with 3).  Two planes per step where n2 is even (26.5 against 28.8
 // ms).  Planes over 1024 points take the fewest rows that fit 1024 threads (40^3: 37.2 ms with C =
 // 2, 40.3 with 3), with one plane per step (two spill: 77 ms).  Planes over 2304 points (and over
 // 2048 unless three rows of 768 threads hold them) have no shape and stay on the complex kernel.
-// RPA_RCOCG_SHAPE="C,Z" forces a shape; RPA_COCG_VERBOSE=1 prints the one launched.
+// RPA_RCOCG_SHAPE="C,Z" forces a streaming shape; RPA_COCG_VERBOSE=1 prints the one launched.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 
-#include "rcocg_kernel.h"
+#include "rres_kernel.h"
 
 namespace rpa {
 
@@ -92,6 +94,42 @@ int per_cu(int bs) { return bs > 512 ? 1 : bs > 320 ? 2 : bs > 192 ? 3 : 4; }
 
 constexpr int kCUs = 256;
 
+// The register-resident kernels where a column and the plane fit (see their instances): real
+// solutions with p and x in registers, else with p and x in memory and up to four waves that fold.
+struct Resident {
+    KernelFn fn = nullptr;
+    bool full = false;
+    int bs = 0, per_cu = 1, half = 0;      // half: vectors of a ring half
+    size_t lds = 0;
+};
+
+// vecs: vectors of pool per workgroup.
+Resident choose_resident(const Grid& g, bool x_complex, int vecs) {
+    Resident r;
+    const char* e = std::getenv("RPA_RCOCG_SHAPE");
+    if (e) return r;                                   // a streaming shape is forced
+    r.lds = rres::lds_fixed() +
+            size_t(2) * rres::kPairs * (g.n1 + 12) * (g.n0 + 16) * sizeof(double2);
+    if (r.lds > 156 * 1024) return r;
+    const int waves = (g.n0 * g.n1 + 63) / 64;
+    if (!x_complex && waves <= 8) r.fn = rres::full_variant(g.n2);
+    if (r.fn) {
+        r.full = true;
+        r.bs = 64 * waves;
+        // workgroups of a CU: LDS, and 8 waves (12 with columns of 12 points)
+        r.per_cu = std::max(1, std::min(int(160 * 1024 / r.lds), (g.n2 <= 12 ? 12 : 8) / waves));
+        return r;
+    }
+    const int most = g.n2 <= 26 ? 12 : 8;
+    for (int half : {rcocg::kRing, rres::kRingHalfMin})
+        if (!r.fn && waves < most && vecs >= 2 * half + rcocg::kSlotExtra) {
+            r.fn = rres::ring_variant(g.n2, x_complex, half);
+            r.half = half;
+        }
+    r.bs = 64 * std::min(most, waves + 4);
+    return r;
+}
+
 }  // namespace
 
 bool rcocg_fits(const Grid& g) { return choose(g).v != nullptr; }
@@ -100,9 +138,16 @@ size_t rcocg_pool_bytes(const Grid& g, int nsys) {
     const Shape s = choose(g);
     if (!s.v) return 0;
     const size_t vec = size_t(g.nd()) * sizeof(double);
-    const size_t slots = std::min(nsys, kCUs * per_cu(s.bs));
-    // launches of few systems get 48 B per point and system and keep a shorter ring
-    return std::min(slots * (rcocg::kRing + rcocg::kSlotExtra) * vec, size_t(nsys) * 6 * vec);
+    // real and complex solutions may take different kernels
+    const int all = 2 * rcocg::kRing + rcocg::kSlotExtra;
+    const Resident re = choose_resident(g, false, all), cx = choose_resident(g, true, all);
+    size_t need = 0;
+    if (!re.fn || !cx.fn)
+        need = size_t(std::min(nsys, kCUs * per_cu(s.bs))) * (rcocg::kRing + rcocg::kSlotExtra);
+    if (cx.fn) need = std::max(need, size_t(std::min(nsys, kCUs)) * all);
+    // where real solutions need no pool, complex ones make do with 48 B per point and system
+    if (re.full) need = std::min(need, size_t(nsys) * 6);
+    return need * vec;
 }
 
 hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
@@ -128,24 +173,31 @@ hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
     a.rhs = L.rhs;
     a.x = L.x;
     a.pool = L.pool;
+    a.xc = L.x_complex ? 1 : 0;
     a.iters = L.iters;
     a.status = L.status;
     a.refinements = L.refinements;
     a.nbuf = s.nbuf;
     a.rs = s.rs;
     a.periodic = L.g.periodic() ? 1 : 0;
-    const KernelFn fn = L.x_complex ? s.v->cplx : s.v->real;
-    const int grid = std::min(L.nsys, kCUs * per_cu(s.bs));
-    const int vecs = int(L.pool_bytes / (size_t(grid) * size_t(a.nd) * sizeof(double)));
-    a.ring = std::min(rcocg::kRing, vecs - rcocg::kSlotExtra);
-    if (a.ring < rcocg::kRingMin) return hipErrorInvalidValue;
+    const size_t vec = size_t(a.nd) * sizeof(double);
+    const Resident res = choose_resident(
+        L.g, L.x_complex, int(L.pool_bytes / (size_t(std::min(L.nsys, kCUs)) * vec)));
+    const KernelFn fn = res.fn ? res.fn : L.x_complex ? s.v->cplx : s.v->real;
+    const int grid = std::min(L.nsys, kCUs * (res.fn ? res.per_cu : per_cu(s.bs)));
+    const size_t lds = res.fn ? res.lds : s.lds;
+    const int bs = res.fn ? res.bs : s.bs;
+    a.ring = res.fn ? 2 * res.half
+                    : std::min(rcocg::kRing, int(L.pool_bytes / (size_t(grid) * vec)) - rcocg::kSlotExtra);
+    if (!res.fn && a.ring < rcocg::kRingMin) return hipErrorInvalidValue;
     if (std::getenv("RPA_COCG_VERBOSE"))
-        std::fprintf(stderr, "rcocg shape C=%d Z=%d bs=%d nbuf=%d grid=%d ring=%d lds=%zu\n", s.v->C,
-                     s.v->Z, s.bs, s.nbuf, grid, a.ring, s.lds);
+        std::fprintf(stderr, "rcocg shape %s C=%d Z=%d bs=%d grid=%d ring=%d lds=%zu\n",
+                     res.full ? "resident" : res.fn ? "resident-ring" : "streaming",
+                     res.fn ? 1 : s.v->C, res.fn ? 2 * rres::kPairs : s.v->Z, bs, grid, a.ring, lds);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(s.lds));
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(s.bs), s.lds, st, a);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(bs), lds, st, a);
     return hipGetLastError();
 }
 

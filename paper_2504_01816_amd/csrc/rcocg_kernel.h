@@ -66,6 +66,7 @@ struct Args {
     int64_t nd;
     const double* rhs;     // system-major, N_d real each
     void* x;               // system-major: N_d real (XS = double) or complex (double2)
+    int xc;                // x is complex (kernels that do not know it by their type)
     double* pool;          // gridDim.x slots of (ring + kSlotExtra) * N_d doubles
     int ring;              // basis vectors kept, kRingMin .. kRing
     int* iters;
@@ -312,14 +313,96 @@ __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* 
     }
 }
 
-// p <- v_j - l_j p, x <- x + e_j p (e = zeta / d) over the m newest basis vectors, in order: the
-// same operations on every point however many steps one update takes, so a solve's bits do not
-// depend on the ring.  The first update starts from x = 0, p = 0, and scales v_1, which is stored
-// as b, by s1 = 1 / |b|.  p is not stored at the end of a solve (done).
+// l_k and e_k = zeta_k / d_k of one step.
 struct Coef {
     double lr, li, er, ei;
 };
 
+// The scalars of one solve: what the reductions of a sweep turn into.  Every value is uniform over
+// the workgroup (wg_reduce), and every thread computes all of them.
+struct Recurrence {
+    double omega, tol2;
+    int max_iter;
+    double sigma = 0.0, delta = 0.0, beta = 0.0, ibeta = 1.0;
+    double sc = 1.0, bn = 0.0, ibn = 0.0, tgt2 = 0.0;        // sc: 1 / |b| while v_1 stands for b
+    double zr = 0.0, zi = 0.0, ir = 0.0, ii = 0.0, b2 = 0.0;  // zeta, 1 / d, beta^2
+    int it = 0, stat = 0;
+    bool done = false;
+
+    __device__ __forceinline__ Recurrence(double w, double t2, int mi)
+        : omega(w), tol2(t2), max_iter(mi) {}
+    __device__ __forceinline__ double cp() const { return it == 0 ? 0.0 : beta * sc; }
+    // acc = (v.w, w.w, v.v) of the sweep.  The first one is on b itself: its sums are scaled to
+    // v_1 = b / |b|.  False for a zero right-hand side.
+    __device__ __forceinline__ bool norms(double (&acc)[3]) {
+        if (it == 0) {
+            if (!(acc[2] > 0.0)) return false;
+            tgt2 = uniform(tol2 * acc[2]);
+            bn = uniform(sqrt(acc[2]));
+            ibn = uniform(1.0 / bn);
+            acc[0] = uniform(acc[0] / acc[2]);
+            acc[1] = uniform(acc[1] / acc[2]);
+        }
+        b2 = uniform(acc[1] - acc[0] * acc[0]);
+        return true;
+    }
+    __device__ __forceinline__ bool cancels(const double (&acc)[3]) const { return b2 < 1e-3 * acc[1]; }
+    // sigma <- alpha; returns delta, which w - delta v removes
+    __device__ __forceinline__ double shift(const double (&acc)[3]) {
+        sigma = uniform(sigma + acc[0]);
+        return acc[0];
+    }
+    __device__ __forceinline__ void reshifted(const double (&ac2)[3], double (&acc)[3]) {
+        const double s1 = it == 0 ? acc[2] : 1.0;
+        acc[0] = uniform(ac2[0] / s1);
+        acc[1] = uniform(ac2[1] / s1);
+        b2 = uniform(acc[1] - acc[0] * acc[0]);
+    }
+    // the factor step; sets done and stat, returns l and zeta / d
+    __device__ __forceinline__ Coef step(const double (&acc)[3]) {
+        sc = it == 0 ? ibn : 1.0;
+        const double alpha = sigma + acc[0];
+        delta = uniform(acc[0]);
+        b2 = b2 > 0.0 ? b2 : (b2 <= 0.0 ? 0.0 : b2);          // NaN stays
+        Coef c;
+        c.lr = uniform(beta * ir);
+        c.li = uniform(beta * ii);
+        const double dr = alpha - beta * c.lr, di = -omega - beta * c.li;
+        if (it == 0) {
+            zr = bn;
+            zi = 0.0;
+        } else {
+            const double t = -(c.lr * zr - c.li * zi);
+            zi = uniform(-(c.lr * zi + c.li * zr));
+            zr = uniform(t);
+        }
+        const double id2 = 1.0 / (dr * dr + di * di);
+        ir = uniform(dr * id2);
+        ii = uniform(-di * id2);
+        c.er = uniform(zr * ir - zi * ii);
+        c.ei = uniform(zr * ii + zi * ir);
+        beta = uniform(sqrt(b2));
+        ibeta = uniform(b2 > 0.0 ? 1.0 / sqrt(b2) : 0.0);
+        sigma = uniform(alpha);
+        const double res2 = b2 * (c.er * c.er + c.ei * c.ei);
+        ++it;
+        if (!(res2 >= 0.0) || !(res2 < INFINITY)) {
+            stat = 2;                                          // not a number: a breakdown
+            done = true;
+        } else if (res2 <= tgt2) {
+            done = true;
+        } else if (it >= max_iter) {
+            stat = 1;
+            done = true;
+        }
+        return c;
+    }
+};
+
+// p <- v_j - l_j p, x <- x + e_j p (e = zeta / d) over the m newest basis vectors, in order: the
+// same operations on every point however many steps one update takes, so a solve's bits do not
+// depend on the ring.  The first update starts from x = 0, p = 0, and scales v_1, which is stored
+// as b, by s1 = 1 / |b|.  p is not stored at the end of a solve (done).
 // REG: the coefficients in registers (else read from LDS at every point).
 template <typename XS, bool REG>
 __device__ __forceinline__ void update_px(int64_t nd, const double* ring, double2* p, XS* x,
@@ -399,39 +482,27 @@ void rcocg_wg(Args a) {
         const double diag = a.cw[0] - a.eps[sys % a.ns];
         const double* b = a.rhs + int64_t(sys) * a.nd;
         XS* x = reinterpret_cast<XS*>(a.x) + int64_t(sys) * a.nd;
-        double sigma = 0.0, delta = 0.0, beta = 0.0, sc = 1.0, tgt2 = 0.0;
-        double lr = 0.0, li = 0.0, zr = 0.0, zi = 0.0, ir = 0.0, ii = 0.0;   // l, zeta, 1/d
-        double ibeta = 1.0, bn = 0.0, ibn = 0.0;
-        int it = 0, stat = 0, slot = 0;               // slot = it mod ring
-        bool done = false, px_first = true, carry = false;
-        bool redo = false;
-        while (!done) {
-            const bool first = it == 0;
+        Recurrence rc(omega, a.tol2, a.max_iter);
+        int slot = 0;                                 // rc.it mod ring
+        bool px_first = true, carry = false, redo = false;
+        while (!rc.done) {
+            const bool first = rc.it == 0;
             double* vnew = ring + slot * a.nd;
             const double* vold = first ? b : ring + ((slot ? slot : a.ring) - 1) * a.nd;
-            // v_k = (w - delta v_{k-1}) / beta; v_1 stays unnormalised (sc = 1 / |b| carries its
-            // norm): the first sweep reads b itself.  A repeated sweep reads the stored v_k.
+            // v_k = (w - delta v_{k-1}) / beta; v_1 stays unnormalised (rc.sc carries its norm): the
+            // first sweep reads b itself.  A repeated sweep reads the stored v_k.
             const bool plain = first || redo;
-            const double c1 = plain ? 1.0 : sc * ibeta;
-            const double c2 = plain ? 0.0 : -delta * sc * ibeta;
-            const double cp = first ? 0.0 : beta * sc;
+            const double c1 = plain ? 1.0 : rc.sc * rc.ibeta;
+            const double c2 = plain ? 0.0 : -rc.delta * rc.sc * rc.ibeta;
             double acc[3] = {0.0, 0.0, 0.0};
-            sweep<C, Z, RAG>(a, rw, planes, diag - sigma, redo ? vnew : (first ? b : w), vold, c1, c2,
-                        cp, vnew, w, Q, carry, acc);
+            sweep<C, Z, RAG>(a, rw, planes, diag - rc.sigma, redo ? vnew : (first ? b : w), vold, c1,
+                             c2, rc.cp(), vnew, w, Q, carry, acc);
             if (RAG) global_barrier();           // w of rows that other threads stored
             wg_reduce<3>(acc, red);
-            if (first) {
-                if (!(acc[2] > 0.0)) break;           // zero right-hand side
-                tgt2 = uniform(a.tol2 * acc[2]);
-                bn = uniform(sqrt(acc[2]));
-                ibn = uniform(1.0 / bn);
-                acc[0] = uniform(acc[0] / acc[2]);
-                acc[1] = uniform(acc[1] / acc[2]);
-            }
-            double b2 = uniform(acc[1] - acc[0] * acc[0]);
-            if (b2 < 1e-3 * acc[1] && !redo) {
+            if (!rc.norms(acc)) break;           // zero right-hand side
+            if (rc.cancels(acc) && !redo) {
                 // cancellation: once more with sigma = alpha
-                sigma = uniform(sigma + acc[0]);
+                rc.shift(acc);
                 carry = false;
 #pragma unroll
                 for (int q = 0; q < 12 + Z; ++q)
@@ -441,49 +512,14 @@ void rcocg_wg(Args a) {
                 continue;
             }
             redo = false;
-            sc = first ? ibn : 1.0;
             carry = a.periodic != 0;
-            const double alpha = sigma + acc[0];
-            delta = uniform(acc[0]);
-            b2 = b2 > 0.0 ? b2 : (b2 <= 0.0 ? 0.0 : b2);      // NaN stays
-            // factor step
-            lr = beta * ir;
-            li = beta * ii;
-            const double dr = alpha - beta * lr, di = -omega - beta * li;
-            if (first) {
-                zr = bn;
-                zi = 0.0;
-            } else {
-                const double t = -(lr * zr - li * zi);
-                zi = -(lr * zi + li * zr);
-                zr = t;
-            }
-            const double id2 = 1.0 / (dr * dr + di * di);
-            ir = uniform(dr * id2);
-            ii = uniform(-di * id2);
-            zr = uniform(zr);
-            zi = uniform(zi);
-            const double er = zr * ir - zi * ii, ei = zr * ii + zi * ir;   // zeta / d
-            if (tid == 0) coef[slot] = Coef{lr, li, er, ei};
-            beta = uniform(sqrt(b2));
-            ibeta = uniform(b2 > 0.0 ? 1.0 / sqrt(b2) : 0.0);
-            sigma = uniform(alpha);
-            const double res2 = b2 * (er * er + ei * ei);
-            ++it;
+            const Coef cf = rc.step(acc);
+            if (tid == 0) coef[slot] = cf;
             const int m = ++slot;                     // basis vectors not yet in x
             if (slot == a.ring) slot = 0;
-            if (!(res2 >= 0.0) || !(res2 < INFINITY)) {
-                stat = 2;                              // not a number: reported as a breakdown
-                done = true;
-            } else if (res2 <= tgt2) {
-                done = true;
-            } else if (it >= a.max_iter) {
-                stat = 1;
-                done = true;
-            }
-            if (done || slot == 0) {
+            if (rc.done || slot == 0) {
                 global_barrier();
-                update_px<XS, true>(a.nd, ring, p, x, coef, m, px_first, ibn, done);
+                update_px<XS, true>(a.nd, ring, p, x, coef, m, px_first, rc.ibn, rc.done);
                 px_first = false;
                 carry = false;              // the queue's registers are free for the update
 #pragma unroll
@@ -493,7 +529,7 @@ void rcocg_wg(Args a) {
                 global_barrier();
             }
         }
-        if (it == 0) {
+        if (rc.it == 0) {
             // zero right-hand side: x = 0 (not a number where b is not finite)
             for (unsigned i = tid; i < unsigned(a.nd); i += BS) {
                 const double v = 0.0 * ld(b, i);
@@ -502,8 +538,8 @@ void rcocg_wg(Args a) {
             }
         }
         if (tid == 0) {
-            a.iters[sys] = it;
-            a.status[sys] = stat;
+            a.iters[sys] = rc.it;
+            a.status[sys] = rc.stat;
             if (a.refinements) a.refinements[sys] = 0;
         }
     }

@@ -1,0 +1,30 @@
+// Instances of the register-resident COCG kernel with p and x in memory (rres_kernel.h).
+#include "rres_kernel.h"
+
+namespace rpa {
+namespace rres {
+
+// Four registers per point of the column (v, w) and about fifty more: 168 per thread (12 waves) hold
+// 26 points, 256 (8 waves) 32.
+KernelFn ring_variant(int nz, bool xc, int half) {
+    if (half == kRingHalfMin && !xc) return nullptr;
+#define RPA_S(N)                                                               \
+    case N: return half == kRingHalfMin ? ring_wg<N, 768, 3, kRingHalfMin, true> \
+                 : xc ? ring_wg<N, 768, 3, kRing, true> : ring_wg<N, 768, 3, kRing, false>;
+#define RPA_A(N) \
+    case N: return xc ? ring_wg<N, 768, 3, kRing, true> : ring_wg<N, 768, 3, kRing, false>;
+#define RPA_B(N) \
+    case N: return xc ? ring_wg<N, 512, 2, kRing, true> : ring_wg<N, 512, 2, kRing, false>;
+    switch (nz) {
+        RPA_S(12) RPA_S(13) RPA_S(14) RPA_S(15) RPA_S(16) RPA_S(17) RPA_S(18) RPA_S(19) RPA_S(20)
+        RPA_A(21) RPA_A(22) RPA_A(23) RPA_A(24) RPA_A(25) RPA_A(26)
+        RPA_B(27) RPA_B(28) RPA_B(29) RPA_B(30) RPA_B(31) RPA_B(32)
+        default: return nullptr;
+    }
+#undef RPA_S
+#undef RPA_A
+#undef RPA_B
+}
+
+}  // namespace rres
+}  // namespace rpa

@@ -1,7 +1,7 @@
 """GPU parity of the real-form COCG kernel (real Lanczos basis, one sweep per iteration) against
 the oracle's complex COCG, at the edges of its launch shapes: the smallest grid, one, two and
-three rows per thread with and without a ragged last row group, odd and even n2, an isolated box,
-iteration caps around the ring of basis vectors, and launches of few and of many systems."""
+three rows per thread with and without a ragged last row group, odd and even n2, the classes of
+the register-resident kernel by column height and plane, an isolated box, iteration caps around the ring of basis vectors, and launches of few and of many systems."""
 import numpy as np
 import pytest
 import torch
@@ -127,3 +127,40 @@ def test_mixed_real_form_is_checked_and_continued(shape, bc):
     assert rc == 0 and st["fp64_fallbacks"] == 4 and st["n_unconverged"] == 0
     assert rel(out.T, ref) < 1e-8
 
+
+@pytest.mark.parametrize("shape,kind", [
+    ((12, 12, 12), "resident"), ((7, 9, 12), "resident"), ((20, 25, 13), "resident"),
+    ((21, 24, 15), "resident"), ((16, 32, 20), "resident"), ((52, 8, 12), "resident"),
+    ((20, 20, 21), "resident-ring"), ((28, 18, 22), "resident-ring"),
+    ((29, 22, 14), "resident-ring"), ((24, 24, 24), "resident-ring"),
+    ((11, 10, 26), "resident-ring"), ((7, 8, 23), "resident-ring"), ((26, 27, 12), "resident-ring"),
+    ((16, 15, 27), "resident-ring"), ((20, 22, 32), "resident-ring"),
+    ((27, 27, 25), "streaming"), ((20, 25, 32), "streaming"), ((12, 12, 33), "streaming")])
+def test_resident_classes(shape, kind, capfd, monkeypatch):
+    # every class edge, periodic and isolated, real solutions and (mixed) complex ones
+    say("resident classes", shape, kind)
+    monkeypatch.setenv("RPA_COCG_VERBOSE", "1")
+    X = np.random.default_rng(12).standard_normal((2, int(np.prod(shape))))
+    for bc in ("periodic", "dirichlet"):
+        c = make(shape, 2, 13, bc)
+        ref, iters, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.4, shape, c.h, 1e-12,
+                                         5000, bc=bc)
+        out, rc, st = chi0(c, X, 0.4, 1e-12)
+        err = capfd.readouterr().err
+        assert "shape %s " % kind in err, err
+        assert rc == 0 and rel(out.T, ref) < 1e-9, rel(out.T, ref)
+        assert abs(st["cocg_iters_total"] - int(iters.sum())) <= iters.size
+        out, rc, st = chi0(c, X, 0.4, 1e-12, precision=1)
+        assert rc == 0 and rel(out.T, ref) < 1e-9 and st["refinements"] == 4
+
+
+@pytest.mark.parametrize("shape", [(16, 18, 17), (23, 24, 19), (30, 30, 30)])
+def test_step_caps_of_every_kernel(shape):
+    # partial solutions after few steps, FP64: resident, resident with a ring, streaming
+    say("caps", shape)
+    c = make(shape, 2, 14)
+    X = np.random.default_rng(15).standard_normal((1, c.nd))
+    for cap in (1, 2, 8, 9):
+        out, rc, st = chi0(c, X, 0.5, 1e-14, cocg_max_iter=cap)
+        ref, _, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.5, shape, c.h, 1e-14, cap)
+        assert rc == 1 and st["cocg_iters_max"] == cap and rel(out.T, ref) < 1e-11
