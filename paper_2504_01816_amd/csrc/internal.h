@@ -78,6 +78,16 @@ hipError_t launch_kron_apply(const Grid& g, int power, int nvec, const double* i
                              double* tmp, const double* Ux, const double* Uy, const double* Uz,
                              const double* kx, const double* ky, const double* kz,
                              hipStream_t s);
+// The same and the preconditioner below in three fused passes (kron.hip), for axes that fit;
+// in == out is allowed.
+bool kron_fused_fits(const Grid& g);
+hipError_t launch_kron_fused(const Grid& g, int power, int nvec, const double* in, double* out,
+                             const double* Ux, const double* Uy, const double* Uz, const double* kx,
+                             const double* ky, const double* kz, hipStream_t s);
+hipError_t launch_kron_fused_precond(const Grid& g, int nsys, const double* in, double* out,
+                                     const double* Ux, const double* Uy, const double* Uz,
+                                     const double* kx, const double* ky, const double* kz,
+                                     const double2* kshift, hipStream_t s);
 // Shifted-Laplacian preconditioner on nsys complex vectors stored as N_d x 2 nsys real
 // columns (real and imaginary part of system t in columns 2t, 2t+1): out = K_t^{-1} in with
 // K_t = -1/2 Lap_h + kshift[t].x - i kshift[t].y, through the same 1D eigenbases.

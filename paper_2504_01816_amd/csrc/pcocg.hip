@@ -17,7 +17,7 @@
 // the 36 neighbours through the caches, where no march shape fits); pc_rz does r^T z and the
 // p update; reductions are workgroup-local and in a fixed order.  z = M r is three
 // LDS-staged passes (x-y planes forward, z pencils with the diagonal scale, x-y planes
-// inverse) over all systems at once for short axes, else 3 + 3 Kronecker GEMM passes with a
+// inverse) over all systems at once for axes up to 64 points, else 3 + 3 Kronecker GEMM passes with a
 // diagonal scale.  Every thread touches the same points in both loops of a kernel, so a
 // value a thread writes is read back only by itself.  Converged systems drop out of the
 // per-system kernels; the host tests for the end every few iterations.
@@ -668,146 +668,6 @@ __global__ __launch_bounds__(BPB) void bc_dir(PcArgs a, int first) {
     }
 }
 
-// ------------------------------------------------------------------ fused preconditioner
-// z = K^{-1} r in three passes instead of six GEMM passes and a scale pass: forward x and y
-// transforms of one z-plane of one system in LDS; forward z transform, diagonal scale and
-// inverse z transform of 64 z-pencils in LDS (results of the forward transform in
-// registers); inverse y and x transforms per plane.  The dense 1D transforms cost n LDS
-// multiply-adds per point and axis, so the fused passes beat the MFMA GEMM passes only for
-// short axes (measured on the whole solve: 1.25x faster than the GEMM passes at 24^3, before
-// the forward x basis was stored transposed, which took the solve from 368 to 313 ms; 118
-// against 70 s at 48^3 after it); used for n0, n1, n2 <= 32.
-constexpr int kFusedMaxXY = 32;
-constexpr int kFusedMaxZ = 32;
-constexpr int kPencils = 64;
-constexpr size_t kMaxLds = 160 * 1024;   // LDS of one workgroup on gfx950
-constexpr int ZB = 512;                      // threads of the pencil pass
-constexpr int XYB = 512;                     // threads of the plane passes
-constexpr int kZr = 64 / (ZB / kPencils);   // z values per thread in the pencil pass (n2 <= 64)
-
-// forward (INV = false): c_(a,b) = sum_(x,y) Ux[x + n0 a] Uy[y + n1 b] f_(x,y); inverse: the
-// transposed bases.  grid (n2, systems), in/out: N_d x 2 nsys split columns.
-template <bool INV>
-__global__ __launch_bounds__(XYB) void pc_xy(const double* in, double* out, int n0, int n1,
-                                            int64_t nd, const double* Ux, const double* Uy) {
-    extern __shared__ double2 shx[];
-    const int P = n0 * n1;
-    const int z = blockIdx.x, t = blockIdx.y;
-    double2* A = shx;
-    double2* B = shx + P;
-    double* ux = reinterpret_cast<double*>(shx + 2 * P);
-    double* uy = ux + n0 * n0;
-    const double* ir = in + nd * (2 * int64_t(t)) + int64_t(z) * P;
-    const double* ii = ir + nd;
-    for (int i = threadIdx.x; i < P; i += XYB) A[i] = double2{ir[i], ii[i]};
-    // x basis stored so that lanes (consecutive a) read consecutive entries: ux[a + n0 k] =
-    // U[a + n0 k] for the inverse, U[k + n0 a] (the transpose) for the forward transform
-    for (int i = threadIdx.x; i < n0 * n0; i += XYB) {
-        const int a = i % n0, k = i / n0;
-        ux[i] = INV ? Ux[i] : Ux[k + n0 * a];
-    }
-    for (int i = threadIdx.x; i < n1 * n1; i += XYB) uy[i] = Uy[i];
-    __syncthreads();
-    for (int o = threadIdx.x; o < P; o += XYB) {          // along x
-        const int y = o / n0, a = o - y * n0;
-        double sr = 0.0, si = 0.0;
-        for (int k = 0; k < n0; ++k) {
-            const double u = ux[a + n0 * k];
-            const double2 v = A[y * n0 + k];
-            sr += u * v.x;
-            si += u * v.y;
-        }
-        B[o] = double2{sr, si};
-    }
-    __syncthreads();
-    for (int o = threadIdx.x; o < P; o += XYB) {          // along y
-        const int b = o / n0, x = o - b * n0;
-        double sr = 0.0, si = 0.0;
-        for (int k = 0; k < n1; ++k) {
-            const double u = INV ? uy[b + n1 * k] : uy[k + n1 * b];
-            const double2 v = B[k * n0 + x];
-            sr += u * v.x;
-            si += u * v.y;
-        }
-        A[o] = double2{sr, si};
-    }
-    __syncthreads();
-    double* orr = out + nd * (2 * int64_t(t)) + int64_t(z) * P;
-    double* oi = orr + nd;
-    for (int i = threadIdx.x; i < P; i += XYB) {
-        orr[i] = A[i].x;
-        oi[i] = A[i].y;
-    }
-}
-
-// In place on the x-y mode coefficients: forward z transform, division by
-// 1/2 (kx + ky + kz) + sigma_t - i omega_t, inverse z transform.  grid (ceil(P/64), systems).
-__global__ __launch_bounds__(ZB) void pc_zscale(double* data, int n0, int n1, int n2, int64_t nd,
-                                                const double* Uz, const double* kx,
-                                                const double* ky, const double* kz,
-                                                const double2* kshift) {
-    extern __shared__ double2 shz[];
-    const int P = n0 * n1;
-    const int g0 = blockIdx.x * kPencils, t = blockIdx.y;
-    const int j = threadIdx.x % kPencils, cg = threadIdx.x / kPencils, ng = ZB / kPencils;
-    double2* Pz = shz;                                          // n2 x 64
-    double* uz = reinterpret_cast<double*>(shz + n2 * kPencils);
-    double* dr = data + nd * (2 * int64_t(t));
-    double* di = dr + nd;
-    for (int e = threadIdx.x; e < n2 * kPencils; e += ZB) {
-        const int zz = e / kPencils, xy = g0 + (e - zz * kPencils);
-        Pz[e] = (xy < P) ? double2{dr[xy + int64_t(P) * zz], di[xy + int64_t(P) * zz]}
-                         : double2{0.0, 0.0};
-    }
-    for (int i = threadIdx.x; i < n2 * n2; i += ZB) uz[i] = Uz[i];
-    __syncthreads();
-    double2 acc[kZr];
-#pragma unroll
-    for (int k = 0; k < kZr; ++k) {
-        const int c = cg + ng * k;
-        double sr = 0.0, si = 0.0;
-        if (c < n2) {
-            for (int zz = 0; zz < n2; ++zz) {
-                const double u = uz[zz + n2 * c];
-                const double2 v = Pz[zz * kPencils + j];
-                sr += u * v.x;
-                si += u * v.y;
-            }
-        }
-        acc[k] = double2{sr, si};
-    }
-    __syncthreads();                                            // every read of Pz done
-    const int xy = g0 + j;
-    const int a = xy % n0, b = (xy / n0) % n1;
-    const double2 ks = kshift[t];
-#pragma unroll
-    for (int k = 0; k < kZr; ++k) {
-        const int c = cg + ng * k;
-        if (c < n2) {
-            const double d = 0.5 * (kx[a] + ky[b] + kz[c]) + ks.x, w = ks.y;
-            const double den = 1.0 / (d * d + w * w);
-            const double2 v = acc[k];
-            Pz[c * kPencils + j] = double2{(v.x * d - v.y * w) * den, (v.y * d + v.x * w) * den};
-        }
-    }
-    __syncthreads();
-    for (int k = 0; k < kZr; ++k) {
-        const int zz = cg + ng * k;
-        if (zz >= n2) break;
-        double sr = 0.0, si = 0.0;
-        for (int c = 0; c < n2; ++c) {
-            const double u = uz[zz + n2 * c];
-            const double2 v = Pz[c * kPencils + j];
-            sr += u * v.x;
-            si += u * v.y;
-        }
-        if (xy < P) {
-            dr[xy + int64_t(P) * zz] = sr;
-            di[xy + int64_t(P) * zz] = si;
-        }
-    }
-}
-
 // ------------------------------------------------------------------ staged step
 // pc_step on the plain COCG kernel's z-march (register queue along z, LDS-staged planes, row
 // slabs for large planes): q = A p in one sweep over the system, then the pointwise x and r
@@ -984,47 +844,19 @@ hipError_t launch_vloc_mean(int64_t nd, const double* vloc, double* out, hipStre
     return hipGetLastError();
 }
 
-// z = K^{-1} r on the first nsys slots: the fused passes where the grid allows, else the
-// Kronecker GEMM passes.
+// z = K^{-1} r on the first nsys slots: the fused passes where the axes fit them, else the
+// Kronecker GEMM passes.  Whole solves, GEMM against fused: 16.8 and 15.0 ms at 48^3 (32 systems),
+// 21.4 and 16.3 at 36^3 (128), 13.5 and 11.5 at 64 x 64 x 16 (64); at 24^3 (1024 systems) the fused
+// passes on the vector units took 41.5 ms, on the matrix cores 32.5.
 hipError_t apply_precond(const PcocgLaunch& L, int nsys, hipStream_t s) {
-    const Grid& g = L.g;
-    // RPA_PRECOND_PASSES=gemm forces the GEMM passes, =lds the fused passes wherever their
-    // LDS and the pencil pass's z range allow (for measurements)
+    // RPA_PRECOND_PASSES=gemm forces the GEMM passes (for measurements)
     static const char* force = std::getenv("RPA_PRECOND_PASSES");
-    const int P = g.n0 * g.n1;
-    const int64_t nd = g.nd();
-    const size_t lxy = size_t(2 * P) * sizeof(double2) +
-                       size_t(g.n0 * g.n0 + g.n1 * g.n1) * sizeof(double);
-    const size_t lz = size_t(g.n2 * kPencils) * sizeof(double2) + size_t(g.n2 * g.n2) * sizeof(double);
-    const bool can = g.n2 <= kZr * (ZB / kPencils) && lxy <= kMaxLds && lz <= kMaxLds &&
-                     nsys <= 65535;
-    const bool fits = can && g.n0 <= kFusedMaxXY && g.n1 <= kFusedMaxXY && g.n2 <= kFusedMaxZ;
-    const bool lds = (force && std::strcmp(force, "lds") == 0) ? can
-                   : (force && std::strcmp(force, "gemm") == 0) ? false
-                   : fits;
-    if (!lds)
-        return launch_kron_precond(g, nsys, L.r, L.z, L.tmp, L.Ux, L.Uy, L.Uz, L.kx, L.ky, L.kz,
-                                   L.kshift, s);
-    hipError_t e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(pc_xy<false>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lxy))) != hipSuccess)
-        return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(pc_xy<true>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lxy))) != hipSuccess)
-        return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(pc_zscale),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lz))) != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(pc_xy<false>, dim3(unsigned(g.n2), unsigned(nsys)), dim3(XYB), lxy, s, L.r,
-                       L.tmp, g.n0, g.n1, nd, L.Ux, L.Uy);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(pc_zscale, dim3(unsigned((P + kPencils - 1) / kPencils), unsigned(nsys)),
-                       dim3(ZB), lz, s, L.tmp, g.n0, g.n1, g.n2, nd, L.Uz, L.kx, L.ky, L.kz,
-                       L.kshift);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(pc_xy<true>, dim3(unsigned(g.n2), unsigned(nsys)), dim3(XYB), lxy, s, L.tmp,
-                       L.z, g.n0, g.n1, nd, L.Ux, L.Uy);
-    return hipGetLastError();
+    const bool gemm = force && std::strcmp(force, "gemm") == 0;
+    if (kron_fused_fits(L.g) && !gemm)
+        return launch_kron_fused_precond(L.g, nsys, L.r, L.z, L.Ux, L.Uy, L.Uz, L.kx, L.ky, L.kz,
+                                         L.kshift, s);
+    return launch_kron_precond(L.g, nsys, L.r, L.z, L.tmp, L.Ux, L.Uy, L.Uz, L.kx, L.ky, L.kz,
+                               L.kshift, s);
 }
 
 // Block COCG: the step kernel stores q = A p for the live slots, the block kernels do the

@@ -1,0 +1,58 @@
+"""GPU checks of the fused Kronecker passes (nu, nu^{1/2} and the preconditioner) at the edges of their
+tiles and compiled lengths: axes of 16, 24, 32, 40, 48 and 64 points and one more, planes of very
+different sides, one vector and more vectors than workgroups, and axes beyond 64 points."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import coulomb as ocoul
+from oracle import precond as opre
+from paper_2504_01816_amd import api, synth
+from paper_2504_01816_amd import lib as L
+from tests.test_gpu_real_form import chi0, make, rel
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+EPS = 2.3e-16
+
+
+@pytest.mark.parametrize("bc", ["periodic", "dirichlet"])
+@pytest.mark.parametrize("shape,nvec", [((7, 8, 12), 1), ((16, 17, 24), 3), ((24, 25, 32), 2),
+                                        ((32, 33, 40), 2), ((41, 40, 16), 2), ((48, 12, 49), 2),
+                                        ((13, 64, 33), 2), ((64, 49, 64), 1), ((12, 65, 12), 2),
+                                        ((11, 9, 12), 2500)])
+def test_coulomb_axes(shape, nvec, bc):
+    c = synth.uniform_cell(shape, 0.45, 0.0)
+    c.bc = bc
+    X = np.random.default_rng(5).standard_normal((nvec, c.nd))
+    dc, Xt = api.device_cell(c, DEV), torch.tensor(X, device=DEV)
+    kap = [ocoul.eigbasis_1d(n, 0.45, bc=bc)[0] for n in shape]
+    low = min(k[k > 1e-9].min() for k in kap) if bc == "periodic" else sum(k[0] for k in kap)
+    for power in (1, 2):
+        out = api.rpa_apply_coulomb(dc, Xt, power)
+        ref = ocoul.nu_apply(X.T, shape, 0.45, power, bc=bc).T
+        # two sides, six products of n terms each, and the relative error that rounded eigenvalues
+        # give to the largest scale, 4 pi / K at the smallest K
+        scale = ocoul.coulomb_scale(shape, 0.45, power, bc=bc).max()
+        bound = scale * EPS * (4 * sum(shape) + 8 * sum(k[-1] for k in kap) / low)
+        err = np.linalg.norm(out.cpu().numpy() - ref, axis=1)
+        assert (err <= bound * np.linalg.norm(X, axis=1)).all(), (power, err.max(), bound)
+        # in place: the same bits
+        Y = Xt.clone()
+        api.rpa_apply_coulomb(dc, Y, power, out=Y)
+        assert torch.equal(Y, out)
+
+
+# two FP64 solvers that meet a residual of 1e-12 differ by cond(A) 1e-12 <= 1e-9 here
+@pytest.mark.parametrize("shape,bc", [((16, 7, 12), "periodic"), ((17, 18, 25), "dirichlet"),
+                                      ((9, 33, 12), "periodic"), ((12, 13, 49), "dirichlet"),
+                                      ((49, 8, 41), "periodic"), ((8, 65, 12), "periodic")])
+def test_preconditioner_axes(shape, bc):
+    c = make(shape, 2, 13, bc)
+    U = np.random.default_rng(14).standard_normal((2, c.nd))
+    out, rc, st = chi0(c, U, 0.7, 1e-12, flags=L.RPA_FLAG_PRECOND)
+    ref, it, _ = opre.chi0_apply_precond(U.T, c.vloc, c.psi.T, c.eps, 0.7, c.shape, c.h, 1e-12, 5000,
+                                         bc=bc)
+    assert rc == 0
+    assert rel(out.T, ref) < 1e-9
+    assert abs(st["cocg_iters_total"] - int(it.sum())) <= it.size
