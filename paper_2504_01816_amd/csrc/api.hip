@@ -340,6 +340,7 @@ void carve_chi0(Carver& cv, const Grid& g, int ns, int nvec, const Opts& o, bool
         const size_t first = (cv.used - size_t(S) * nd * (b.mixed ? 24 : 40)) / 256 * 256 + 256;
         b.pool_bytes = rcocg_pool_bytes(g, S);
         if (first + b.pool_bytes > cv.used) cv.take<char>(first + b.pool_bytes - cv.used);
+        else b.pool_bytes = cv.used - first;         // a longer ring where the room is there
         if (cv.base) b.pool = reinterpret_cast<double*>(cv.base + first);
     }
     b.x = cv.take<char>(size_t(S) * nd * (b.x_complex ? 16 : 8));

@@ -53,8 +53,10 @@ void stencil_weights(double h, double cw[7]) {
     for (int k = 1; k <= 6; ++k) cw[k] = -0.5 * w[k] * ih2;
 }
 
+constexpr size_t kLds = 160 * 1024;
+
 size_t lds_bytes(const Grid& g, int C, int Z, int nbuf, int rs) {
-    return 16 * 3 * sizeof(double) + rcocg::kRing * sizeof(rcocg::Coef) + 16 +
+    return 16 * 3 * sizeof(double) + rcocg::kRingLong * sizeof(rcocg::Coef) + 16 +
            size_t(nbuf) * Z * (g.n1 + 11 + C) * rs * sizeof(double);
 }
 
@@ -74,12 +76,13 @@ Shape choose(const Grid& g) {
         s.v = &v;
         s.bs = bs;
         s.rs = (g.n0 + 12 + 7) / 8 * 8;
-        s.lds = lds_bytes(g, v.C, v.Z, 2, s.rs);
-        if (s.lds > 150 * 1024) {
+        const size_t delay = v.C > 1 ? size_t(rcocg::kDelay) * v.C * bs * sizeof(double) : 0;
+        s.lds = lds_bytes(g, v.C, v.Z, 2, s.rs) + delay;
+        if (s.lds > kLds) {
             s.nbuf = 1;
-            s.lds = lds_bytes(g, v.C, v.Z, 1, s.rs);
+            s.lds = lds_bytes(g, v.C, v.Z, 1, s.rs) + delay;
         }
-        if (s.lds > 150 * 1024) continue;
+        if (s.lds > kLds) continue;
         const double cost = double(bs - cols) / bs + 0.1 * (2 - v.Z) + 0.05 * v.C;
         if (cost < best_cost) {
             best_cost = cost;
@@ -143,6 +146,7 @@ size_t rcocg_pool_bytes(const Grid& g, int nsys) {
     const Resident re = choose_resident(g, false, all), cx = choose_resident(g, true, all);
     size_t need = 0;
     if (!re.fn || !cx.fn)
+        // a ring of kRing; kRingLong is for launches that fill the chip, and these have the room
         need = size_t(std::min(nsys, kCUs * per_cu(s.bs))) * (rcocg::kRing + rcocg::kSlotExtra);
     if (cx.fn) need = std::max(need, size_t(std::min(nsys, kCUs)) * all);
     // where real solutions need no pool, complex ones make do with 48 B per point and system
@@ -188,7 +192,7 @@ hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
     const size_t lds = res.fn ? res.lds : s.lds;
     const int bs = res.fn ? res.bs : s.bs;
     a.ring = res.fn ? 2 * res.half
-                    : std::min(rcocg::kRing, int(L.pool_bytes / (size_t(grid) * vec)) - rcocg::kSlotExtra);
+                    : std::min(rcocg::kRingLong, int(L.pool_bytes / (size_t(grid) * vec)) - rcocg::kSlotExtra);
     if (!res.fn && a.ring < rcocg::kRingMin) return hipErrorInvalidValue;
     if (std::getenv("RPA_COCG_VERBOSE"))
         std::fprintf(stderr, "rcocg shape %s C=%d Z=%d bs=%d grid=%d ring=%d lds=%zu\n",

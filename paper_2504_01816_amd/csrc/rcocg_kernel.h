@@ -13,14 +13,15 @@
 //
 // What bounds it: memory.  COCG on complex vectors moves r, p, x twice through two sweeps
 // (120 B per point-iteration measured at 24^3, 161 B at 48^3).  Here one sweep per iteration
-// reads w and v_k and writes v_{k+1} and w (32 B), and p and x are updated once per m <= kRing
+// reads w and v_k and writes v_{k+1} and w (32 B), and p and x are updated once per m <= kRingLong
 // iterations from the last m basis vectors, which a ring keeps (8 + 48 / m B per
-// point-iteration).
+// point-iteration; m = 16 instead of 8: 43.7 -> 41.9 ms at 48^3, 83.4 -> 81.5 ms at 32^3, the
+// launches below).
 //
 //  * sigma is the previous alpha, so |w|^2 - delta^2 does not cancel; where it does (first step,
 //    b close to an eigenvector) the sweep is repeated with sigma = alpha.
 //  * One workgroup owns a system for its whole solve and takes the next one from a counter, in
-//    dispatch order; its vectors live in a slot of the state pool (kRing ring vectors, w, p).
+//    dispatch order; its vectors live in a slot of the state pool (ring vectors, w, p).
 //  * A sweep marches along z.  A thread owns C consecutive rows of the x-y plane at one x and
 //    keeps planes z-6 .. z+5+Z of v_{k+1} in registers; the current planes are staged in LDS with
 //    ghost columns and rows.  The C rows share their y neighbours: 12 + 12 / C LDS reads per
@@ -32,7 +33,7 @@
 //
 // Measured, chi0 block-applies, the two-sweep complex kernel against this one: 24^3, 1024
 // systems, omega 0.02, tol 1e-10: 62.2 -> 26.5 ms (5.4 TB/s); 48^3, 1024 systems, omega 8.8, tol
-// 1e-8: 136 -> 48 ms; 32^3, 2 x 1024 systems with complex solutions: 217 -> 84 ms.
+// 1e-8: 136 -> 42 ms; 32^3, 2 x 1024 systems with complex solutions: 217 -> 81 ms.
 #pragma once
 
 #include <type_traits>
@@ -48,8 +49,10 @@ using cocg::st;
 using cocg::uniform;
 using cocg::wg_reduce;
 
-constexpr int kRing = 8;       // most basis vectors kept between two updates of p and x
+constexpr int kRing = 8;       // basis vectors of one half of a resident kernel's ring
+constexpr int kRingLong = 16;  // most basis vectors kept between two updates of p and x here
 constexpr int kRingMin = 2;    // the sweep reads v_k and writes v_{k+1}
+constexpr int kDelay = 5;      // planes of v_k between lead and centre that LDS holds (C > 1)
 constexpr int kSlotExtra = 3;  // vectors of a slot besides the ring: w, complex p
 
 struct Args {
@@ -68,7 +71,7 @@ struct Args {
     void* x;               // system-major: N_d real (XS = double) or complex (double2)
     int xc;                // x is complex (kernels that do not know it by their type)
     double* pool;          // gridDim.x slots of (ring + kSlotExtra) * N_d doubles
-    int ring;              // basis vectors kept, kRingMin .. kRing
+    int ring;              // basis vectors kept, kRingMin .. kRingLong
     int* iters;
     int* status;
     int* refinements;      // written 0 per system if not null
@@ -167,15 +170,19 @@ template <int C, int Z, bool RAG>
 __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* planes,
                                       double diag0, const double* lw, const double* lv,
                                       double cw, double cv, double cp, double* vout, double* wout,
-                                      double (&Q)[12 + Z][C], bool warm, double (&acc)[3]) {
+                                      double (&Q)[12 + Z][C], bool warm, double (&acc)[3],
+                                      double* delay) {
     const int n2 = a.n2, P = a.P, rs = a.rs, n0 = a.n0, n1 = a.n1;
-    // lv at the centre planes: with one row per thread a second queue holds it from the lead
-    // plane on; with more there are no registers for it (48^3, C = 3, 1024
-    // systems at omega 8.8: spilled, 163 ms against 48) and it is read again, a few planes later
-    // and so mostly from the caches
+    // lv at the centre planes: with one row per thread a second queue holds it from the lead plane
+    // on; with more there are no registers for it (48^3, C = 3: spilled, 163 ms against 48), and the
+    // thread's own values wait in LDS, the newest plane in H (read again from memory: 48.3
+    // ms instead of 43.7)
     constexpr bool UQ = C == 1;
-    constexpr int NU = UQ ? 6 + Z : Z;
-    double U[NU][C];
+    static_assert(UQ || Z == 1, "the delay line advances one plane per step");
+    constexpr int NU = UQ ? 6 + Z : 1;
+    double U[NU][C], H[C];
+    const int BS = blockDim.x;
+    double* dl = delay + threadIdx.x * C;    // [plane mod kDelay][BS][C]
     const int PL = (n1 + 11 + C) * rs;
     const bool per = a.periodic != 0;
     constexpr int kWarm = C == 1 ? 6 : 3;    // planes of w loaded together
@@ -196,6 +203,8 @@ __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* 
                 for (int i = 0; i < C; ++i) {
                     const double vo = Q[s0 + s][i];
                     if (UQ && s0 + s >= 6) U[(s0 + s + 6) % 12 % NU][i] = vo;
+                    if (!UQ && s0 + s == 11) H[i] = vo;
+                    if (!UQ && s0 + s >= 6 && s0 + s < 11) dl[(s0 + s - 6) * BS * C + i] = vo;
                     Q[s0 + s][i] = vnext(cw, t[s][i], cv, vo);
                 }
         }
@@ -218,12 +227,14 @@ __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* 
             for (int i = 0; i < C; ++i) {
                 Q[s][i] = vnext(cw, w[i], cv, v[i]);
                 if (UQ && s >= 6) U[(s + 6) % 12 % NU][i] = v[i];
+                if (!UQ && s == 11) H[i] = v[i];
+                if (!UQ && s >= 6 && s < 11) dl[(s - 6) * BS * C + i] = v[i];
             }
             // one plane's loads at a time: a cold start is rare, its registers are not
             asm volatile("" ::: "memory");
         }
     }
-    double LW[Z][C], LV[Z][C], PV[Z][C], UV[Z][C];
+    double LW[Z][C], LV[Z][C], PV[Z][C];
     // lead planes zo + 6 + zz of the step at zo, and V_loc of its centre planes
     auto fetch = [&](int zo) {
 #pragma unroll
@@ -244,14 +255,12 @@ __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* 
                 }
             }
 #pragma unroll
-            for (int i = 0; i < C; ++i) {
-                PV[zz][i] = ld(a.vloc + (zo + zz) * P, rw.col[i]);
-                if constexpr (!UQ) UV[zz][i] = ld(lv + (zo + zz) * P, rw.col[i]);
-            }
+            for (int i = 0; i < C; ++i) PV[zz][i] = ld(a.vloc + (zo + zz) * P, rw.col[i]);
         }
     };
     fetch(0);
     const int nsteps = n2 / Z;
+    int du = 0;                              // zo mod kDelay
 #pragma unroll 1
     for (int stp = 0; stp < nsteps; ++stp) {
         const int zo = stp * Z;
@@ -263,11 +272,18 @@ __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* 
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 Q[12 + zz][i] = vnext(c1, LW[zz][i], cv, LV[zz][i]);
-                if constexpr (UQ) U[6 + zz][i] = LV[zz][i];
-                else U[zz][i] = UV[zz][i];
+                if constexpr (UQ) {
+                    U[6 + zz][i] = LV[zz][i];
+                } else {
+                    double* d = dl + du * BS * C + i;
+                    U[0][i] = *d;
+                    *d = H[i];
+                    H[i] = LV[zz][i];
+                }
                 VV[zz][i] = PV[zz][i];
             }
         }
+        du = du + 1 == kDelay ? 0 : du + 1;
         // ragged: the fetches past the top read v of rows that other threads stored
         if (RAG && zo + Z + 6 <= n2 && zo + 2 * Z + 6 > n2) global_barrier();
         if (stp + 1 < nsteps) fetch(zo + Z);
@@ -404,21 +420,21 @@ struct Recurrence {
 // depend on the ring.  The first update starts from x = 0, p = 0, and scales v_1, which is stored
 // as b, by s1 = 1 / |b|.  p is not stored at the end of a solve (done).
 // REG: the coefficients in registers (else read from LDS at every point).
-template <typename XS, bool REG>
+template <typename XS, bool REG, int M>
 __device__ __forceinline__ void update_px(int64_t nd, const double* ring, double2* p, XS* x,
                                           const Coef* coef, int m, bool first, double s1,
                                           bool done) {
     constexpr bool CX = std::is_same<XS, double2>::value;
     const unsigned n = unsigned(nd);
-    Coef cr[REG ? kRing : 1];
+    Coef cr[REG ? M : 1];
     if constexpr (REG) {
 #pragma unroll
-        for (int j = 0; j < kRing; ++j) cr[j] = coef[j < m ? j : 0];
+        for (int j = 0; j < M; ++j) cr[j] = coef[j < m ? j : 0];
     }
     for (unsigned i = threadIdx.x; i < n; i += blockDim.x) {
-        double v[kRing];
+        double v[M];
 #pragma unroll
-        for (int j = 0; j < kRing; ++j)
+        for (int j = 0; j < M; ++j)
             if (j < m) v[j] = ld(ring + j * nd, i);
         double2 pv{0.0, 0.0};
         double xr = 0.0, xi = 0.0;
@@ -435,7 +451,7 @@ __device__ __forceinline__ void update_px(int64_t nd, const double* ring, double
             }
         }
 #pragma unroll
-        for (int j = 0; j < kRing; ++j) {
+        for (int j = 0; j < M; ++j) {
             if (j < m) {
                 if constexpr (!REG) asm volatile("" ::: "memory");
                 const Coef c = REG ? cr[REG ? j : 0] : coef[j];
@@ -459,8 +475,9 @@ void rcocg_wg(Args a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double* red = reinterpret_cast<double*>(smem_raw);                 // 16 waves x 3
     Coef* coef = reinterpret_cast<Coef*>(smem_raw + 16 * 3 * sizeof(double));
-    int* next = reinterpret_cast<int*>(coef + kRing);
-    double* planes = reinterpret_cast<double*>(coef + kRing) + 2;
+    int* next = reinterpret_cast<int*>(coef + kRingLong);
+    double* planes = reinterpret_cast<double*>(coef + kRingLong) + 2;
+    double* delay = planes + a.nbuf * Z * (a.n1 + 11 + C) * a.rs;
     const int tid = threadIdx.x, BS = blockDim.x;
     const Rows<C> rw = make_rows<C, RAG>(a.n0, a.n1);
     {   // ghost entries outside an isolated box read zero
@@ -496,7 +513,7 @@ void rcocg_wg(Args a) {
             const double c2 = plain ? 0.0 : -rc.delta * rc.sc * rc.ibeta;
             double acc[3] = {0.0, 0.0, 0.0};
             sweep<C, Z, RAG>(a, rw, planes, diag - rc.sigma, redo ? vnew : (first ? b : w), vold, c1,
-                             c2, rc.cp(), vnew, w, Q, carry, acc);
+                             c2, rc.cp(), vnew, w, Q, carry, acc, delay);
             if (RAG) global_barrier();           // w of rows that other threads stored
             wg_reduce<3>(acc, red);
             if (!rc.norms(acc)) break;           // zero right-hand side
@@ -519,7 +536,7 @@ void rcocg_wg(Args a) {
             if (slot == a.ring) slot = 0;
             if (rc.done || slot == 0) {
                 global_barrier();
-                update_px<XS, true>(a.nd, ring, p, x, coef, m, px_first, rc.ibn, rc.done);
+                update_px<XS, false, kRingLong>(a.nd, ring, p, x, coef, m, px_first, rc.ibn, rc.done);
                 px_first = false;
                 carry = false;              // the queue's registers are free for the update
 #pragma unroll

@@ -490,7 +490,7 @@ void ring_wg(Args a) {
         } else {
             // the vectors since the last full half, by every wave
             global_barrier();
-            rcocg::update_px<X, false>(a.nd, ring + half * M * a.nd, p, x, coef + half * kRing, slot,
+            rcocg::update_px<X, false, kRing>(a.nd, ring + half * M * a.nd, p, x, coef + half * kRing, slot,
                                        none, rc.ibn, true);
         }
         finish(a, sys, rc);

@@ -164,3 +164,23 @@ def test_step_caps_of_every_kernel(shape):
         out, rc, st = chi0(c, X, 0.5, 1e-14, cocg_max_iter=cap)
         ref, _, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.5, shape, c.h, 1e-14, cap)
         assert rc == 1 and st["cocg_iters_max"] == cap and rel(out.T, ref) < 1e-11
+
+
+@pytest.mark.parametrize("shape", [(12, 12, 33), (35, 37, 12), (46, 47, 12)])
+@pytest.mark.parametrize("cap", [1, 8, 9, 15, 16, 17, 33])
+def test_streaming_iteration_caps(shape, cap):
+    # the partial solution after `cap` steps of the streaming kernel with one, two and three rows per
+    # thread, in launches that keep a ring of 16 vectors (five vectors per system, 256 workgroups)
+    # and in ones that keep 8: part full, full and just reused; the solves give the same bits
+    say("streaming cap", shape, cap)
+    c = make(shape, 2, 15)
+    X = np.random.default_rng(16).standard_normal((2, c.nd))
+    many, rc, st = chi0(c, np.concatenate([X] * 244), 0.5, 1e-14, cocg_max_iter=cap)
+    ref, _, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, 0.5, c.shape, c.h, 1e-14, cap)
+    few, _, _ = chi0(c, X, 0.5, 1e-14, cocg_max_iter=cap)
+    assert rc == 1 and st["cocg_iters_max"] == cap
+    assert rel(many[-2:].T, ref) < 1e-11 and rel(few.T, ref) < 1e-11
+    # the projections of both launches are summed in as many parts (128 points each, at most 2048
+    # over the tiles of 64 systems), so the right-hand sides are the same bits too
+    if c.nd // 128 <= 2048 // 16:
+        assert np.array_equal(many[:2], few) and np.array_equal(many[-2:], few)
