@@ -987,7 +987,7 @@ int chol_orthonormalize(const Grid& g, int nr, const double* R, double* V, SubBu
                         hipStream_t s) {
     const int64_t nd = g.nd();
     RPA_HIP(launch_gram(nd, nr, R, R, b.part, b.gsplit, b.M, s));
-    RPA_HIP(launch_chol_inv(nr, b.M, b.L, b.T, b.info, s));
+    RPA_HIP(launch_chol_inv(nr, b.M, b.L, b.T, b.info, MatrixList(), s));
     int info = 0;
     RPA_HIP(hipMemcpyAsync(&info, b.info, sizeof(int), hipMemcpyDeviceToHost, s));
     RPA_HIP(hipStreamSynchronize(s));
@@ -1023,7 +1023,8 @@ int subspace_iter(const rpa_cell* cell, const Grid& g, double omega, double weig
             RPA_HIP(launch_sq_energy(nr, b.C, o.sq_order, weight / (2.0 * M_PI), b.ework, b.escal,
                                      b.info, s));
         else
-            RPA_HIP(launch_energy_logdet(nr, b.C, weight / (2.0 * M_PI), b.ework, b.escal, b.info, s));
+            RPA_HIP(launch_energy_logdet(nr, b.C, b.ework, b.escal, b.info,
+                                         MatrixList(0, weight / (2.0 * M_PI)), s));
         int info = 0;
         RPA_HIP(hipMemcpyAsync(&E, b.escal, sizeof(double), hipMemcpyDeviceToHost, s));
         RPA_HIP(hipMemcpyAsync(&info, b.info, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1080,7 +1081,7 @@ int energy_batched(const rpa_cell* cell, int nr, int nfreq, const double* omega,
     // V0 -> orthonormal start (Cholesky-QR, as in the warm driver)
     {
         RPA_HIP(launch_gram(nd, nr, V0, V0, b.part, b.gsplit, b.M, s));
-        RPA_HIP(launch_chol_inv(nr, b.M, b.L, b.T, b.info, s));
+        RPA_HIP(launch_chol_inv(nr, b.M, b.L, b.T, b.info, MatrixList(), s));
         int info = 0;
         RPA_HIP(hipMemcpyAsync(&info, b.info, sizeof(int), hipMemcpyDeviceToHost, s));
         RPA_HIP(hipStreamSynchronize(s));
@@ -1118,11 +1119,17 @@ int energy_batched(const rpa_cell* cell, int nr, int nfreq, const double* omega,
             if (o.sq_order > 0)
                 RPA_HIP(launch_sq_energy(nr, C, o.sq_order, weight[f] / (2.0 * M_PI), b.ework,
                                          b.escal + 8 * f, b.info + 8 * f, s));
-            else
-                RPA_HIP(launch_energy_logdet(nr, C, weight[f] / (2.0 * M_PI), b.ework,
-                                             b.escal + 8 * f, b.info + 8 * f, s));
             RPA_HIP(launch_gram(nd, nr, b.R + a * blk, b.R + a * blk, b.part, b.gsplit, b.M + f * sq, s));
-            RPA_HIP(launch_chol_inv(nr, b.M + f * sq, b.L + f * sq, b.T + f * sq, b.info + 8 * f + 1, s));
+        }
+        // the dense algebra of all frequencies together
+        for (int a0 = 0; a0 < na; a0 += MatrixList::kMost) {
+            MatrixList at;
+            at.clear();
+            for (int a = a0; a < std::min(na, a0 + MatrixList::kMost); ++a)
+                at.add(active[a], weight[active[a]] / (2.0 * M_PI));
+            if (o.sq_order <= 0)
+                RPA_HIP(launch_energy_logdet(nr, b.C, b.ework, b.escal, b.info, at, s));
+            RPA_HIP(launch_chol_inv(nr, b.M, b.L, b.T, b.info + 1, at, s));
         }
         RPA_HIP(hipMemcpyAsync(escal.data(), b.escal, sizeof(double) * 8 * nfreq,
                                hipMemcpyDeviceToHost, s));

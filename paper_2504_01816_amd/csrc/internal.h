@@ -239,13 +239,26 @@ hipError_t launch_gemm_tall_small(int64_t nd, int m, const double* A, const doub
                                   double* Y, hipStream_t s);
 // Symmetrise C <- (C + C^T)/2 (in place).
 hipError_t launch_symmetrize(int m, double* C, hipStream_t s);
+// The matrices a launch works on: matrix f of an array of m x m ones, its info and E at 8 f.
+struct MatrixList {
+    static constexpr int kMost = 32;
+    int n = 0;
+    int f[kMost];
+    double scale[kMost];
+    explicit MatrixList(int f0 = 0, double s0 = 1.0) { add(f0, s0); }
+    void add(int fi, double si) {
+        f[n] = fi;
+        scale[n++] = si;
+    }
+    void clear() { n = 0; }
+};
 // Lower Cholesky of M (in place into L, upper part zeroed) then T = L^{-T} (upper).
 // info[0] = 0 on success, k+1 if the k-th pivot is not positive.
 hipError_t launch_chol_inv(int m, const double* M, double* L, double* T, int* info,
-                           hipStream_t s);
+                           const MatrixList& at, hipStream_t s);
 // E = scale * (ln det(I - C) + tr C) via Cholesky of I - C; out[0] = E, info[0] as above.
-hipError_t launch_energy_logdet(int m, const double* C, double scale, double* work,
-                                double* out, int* info, hipStream_t s);
+hipError_t launch_energy_logdet(int m, const double* C, double* work, double* out, int* info,
+                                const MatrixList& at, hipStream_t s);
 // Gauss spectral quadrature of order n_o (1..32): E = scale * sum_r e_r^T g(C) e_r by n_o
 // Lanczos steps from each e_r; work >= m + 1 doubles; out[0] = E, info[0] = 0 (1: not finite).
 hipError_t launch_sq_energy(int m, const double* C, int n_o, double scale, double* work,

@@ -28,7 +28,9 @@ import os
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("csrc/cocg_kernel.h", "csrc/cocg.hip", "csrc/cocg_f64.hip", "csrc/cocg_mixed.hip")
+KERNEL_SOURCES = ("csrc/cocg_kernel.h", "csrc/cocg.hip", "csrc/cocg_f64.hip", "csrc/cocg_mixed.hip",
+                  "csrc/rcocg_kernel.h", "csrc/rcocg.hip", "csrc/rres_kernel.h", "csrc/rres_full.hip",
+                  "csrc/rres_ring.hip")
 
 
 def kernel_source_hash():

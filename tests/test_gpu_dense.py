@@ -10,6 +10,7 @@ import torch
 from oracle import coulomb as ocoul
 from oracle import gradient as ograd
 from paper_2504_01816_amd import api, synth
+from paper_2504_01816_amd import lib as L
 from tests.test_gpu_real_form import make
 
 pytestmark = pytest.mark.gpu
@@ -64,3 +65,19 @@ def test_box_bases(shape):
         out = api.rpa_apply_coulomb(api.device_cell(c, DEV), torch.tensor(X, device=DEV), power)
         ref = ocoul.nu_apply(X.T, shape, 0.45, power, bc="dirichlet").T
         assert np.abs(out.cpu().numpy() - ref).max() < 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("nfreq,nr", [(1, 5), (32, 5), (33, 5), (3, 121)])
+def test_batched_frequencies_share_the_dense_launches(nfreq, nr):
+    # every frequency's energy as in a run of its own: lists of 32 matrices, and beyond 120 columns
+    # one work matrix for all
+    c = make((8, 7, 12), 2, 17)
+    V0 = np.random.default_rng(18).standard_normal((nr, c.nd))
+    om, wt = np.linspace(0.5, 6.0, nfreq), np.linspace(1.0, 2.0, nfreq)
+    opts = dict(cocg_tol=1e-12, subspace_iters=2, ec_tol=0.0, freq_mode=L.RPA_INDEPENDENT)
+    dc, V = api.device_cell(c, DEV), torch.tensor(V0, device=DEV)
+    E = api.rpa_energy(dc, nr, om, wt, [V], opts)["E_freq"][0].tolist()
+    for f in {0, nfreq // 2, nfreq - 1}:
+        one = api.rpa_energy(dc, nr, om[f:f + 1], wt[f:f + 1], [V], opts)["E_freq"][0].tolist()
+        # the solves meet 1e-12; the energy moves by cond(A) times that at most
+        assert abs(E[f] - one[0]) <= 1e-9 * abs(one[0]), (f, E[f], one[0])
