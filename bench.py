@@ -32,13 +32,46 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # algorithmic bytes per grid point per COCG iteration: read and write x, r, p
 ALG_BYTES = {"fp64": 96.0, "mixed": 48.0}
+# bytes per grid point per iteration that the real-form kernels move by design: a sweep reads w and
+# v_k and writes v_{k+1} and w (32), a ring vector is read once more (8), complex p and x are read
+# and written once per 16 iterations (3); with v, w and V_loc in registers a ring vector is written
+# and read once (16), p and x once per 8 (6)
+REAL_FORM_BYTES = {"streaming": 43.0, "resident": 22.0}
+
+
+def real_form_kernel(precision, shape, min_omega):
+    """The real-form kernel that solves on a grid of this shape: "streaming", "resident", or None
+    where the complex kernels do (a complex64 recurrence at every frequency, planes beyond 48 x 48
+    points, a forced launch shape)."""
+    if (precision == "mixed" and min_omega <= 0.0) or "RPA_COCG_SHAPE" in os.environ:
+        return None
+    n0, n1, n2 = shape
+    if n0 * n1 > 2304:
+        return None
+    return "resident" if n0 * n1 <= 704 and n2 <= 26 else "streaming"
+
+
+def alg_bytes(precision, shape, min_omega):
+    """Algorithmic bytes per point and iteration of the kernel that runs."""
+    kind = real_form_kernel(precision, shape, min_omega)
+    return REAL_FORM_BYTES[kind] if kind else ALG_BYTES[precision]
+
+
+def kernel_name(precision, shape, min_omega):
+    kind = real_form_kernel(precision, shape, min_omega)
+    if kind:
+        return ("%s (batched COCG in its real Lanczos form, one workgroup per system)" %
+                {"streaming": "rcocg_wg", "resident": "ring_wg"}[kind])
+    return ("cocg_wg<%s> (batched COCG, one workgroup per system)" %
+            ("float, float2" if precision == "mixed" else "double, double"))
 
 
 def host_driven_bytes(precond, block, shape):
     """Algorithmic HBM bytes per point and system-iteration of the host-driven solvers: the
     step (q = A p; with the x and r updates for single systems: 128 B) and its direction update
     (r^T z and p: 64 B), or the block kernels (q = A p 32 B, alpha step 128 B, beta step 80 B);
-    the preconditioner adds 32 B per pass, 3 fused passes for axes <= 32, else 7."""
+    the preconditioner adds 32 B per pass: 3 fused passes for axes <= 32, else priced at the 7
+    of the general products (axes up to 64 take the fused passes as well)."""
     b = 240.0 if block >= 2 else 192.0
     if precond:
         b += 32.0 * (3 if max(shape) <= 32 else 7)
@@ -287,9 +320,10 @@ def run_cycle(args):
     torch.cuda.synchronize()
     T = time.perf_counter() - T0
     applies = sum(s["chi0_applies"] for s in steps)
-    # Two kernels run the COCG of the timed steps: the precision's own (complex64 in the mixed
-    # path) and, in the mixed path, the FP64 one for the steps below mixed_min_omega.  Each
-    # class is priced at its own algorithmic bytes over the steps whose only COCG launch is
+    # Two classes of steps: the precision's own (in the mixed path the real-form FP64 kernel with an
+    # exact residual per system, or the complex64 kernel where that does not run) and, in the mixed
+    # path, the plain FP64 solves of the steps below mixed_min_omega.  Each
+    # class is priced at its own kernel's algorithmic bytes over the steps whose only COCG launch is
     # that kernel (a step with FP64 continuations adds FP64 launches and is left out); the
     # roofline reports the class with the larger share of the timed region's kernel time.
     min_om = (args.mixed_min_omega if args.mixed_min_omega >= 0
@@ -305,14 +339,15 @@ def run_cycle(args):
         cocg_ms = sum(s["cocg_kernel_ms"] for s in rsteps)
         pit = sum(s["cocg_point_iters"] for s in rsteps)
         launches = len(rsteps)
-        alg_pp = ALG_BYTES[p]
+        # a mixed step below mixed_min_omega runs the FP64 kernel
+        shape, lowest = wl.cells[0].shape, min_om if p == "mixed" else 0.0
+        alg_pp = alg_bytes(p, shape, lowest)
         achieved = alg_pp * pit / (cocg_ms * 1e-3) / 1e9 if cocg_ms > 0 else 0.0
         avg_ms = cocg_ms / max(1, launches)
         traffic, tb = cocg_traffic(wl.name, p, pit / max(1, launches))
         entry = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                  "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                 "kernel": "cocg_wg<%s> (batched COCG, one workgroup per system)" % (
-                     "float, float2" if p == "mixed" else "double, double"),
+                 "kernel": kernel_name(p, shape, lowest),
                  "launches": launches, "avg_launch_ms": avg_ms,
                  "launch_omegas": ["%.4g" % wl.omegas[s["m"]] for s in rsteps],
                  # this kernel's dispatches of the timed region within the whole run, in
@@ -363,6 +398,8 @@ def run_cycle(args):
     ec = {}
     others = [args.precision] + ([p for p in ("mixed", "fp64") if p != args.precision]
                                  if args.compare == "other" else [])
+    least_omega = (args.mixed_min_omega if args.mixed_min_omega >= 0
+                   else L.default_options().mixed_min_omega)
     for p in others:
         o = dict(opts(p), subspace_iters=args.ec_iters, freq_mode=L.RPA_INDEPENDENT)
         torch.cuda.synchronize()
@@ -375,7 +412,8 @@ def run_cycle(args):
                      chi0_block_applies_per_s=st["chi0_applies"] / t,
                      cocg_iters_total=st["cocg_iters_total"], cocg_iters_max=st["cocg_iters_max"],
                      fp64_fallbacks=st["fp64_fallbacks"], refinements=st["refinements"],
-                     cocg_alg_GBs=ALG_BYTES[p] * st["cocg_point_iters"] / (st["cocg_kernel_ms"] * 1e-3) / 1e9,
+                     cocg_alg_GBs=alg_bytes(p, wl.cells[0].shape, least_omega) *
+                     st["cocg_point_iters"] / (st["cocg_kernel_ms"] * 1e-3) / 1e9,
                      subspace_iters_per_freq=args.ec_iters, E_freq=r["E_freq"][0].tolist())
         print("[bench] time-to-E_c %s: %.2f s, E_c %.12e, iterations %d (max %d)" % (
             p, t, ec[p]["E_c"], st["cocg_iters_total"], st["cocg_iters_max"]), file=sys.stderr,
@@ -493,7 +531,8 @@ def run_energy(args):
     cocg_ms = sum(s["cocg_ms"] for s in steps)
     pit = sum(s["point_iters"] for s in steps)
     launches = sum(s["launches"] for s in steps)
-    alg_pp = ALG_BYTES[args.precision]
+    min_om = opts.get("mixed_min_omega", L.default_options().mixed_min_omega)
+    alg_pp = alg_bytes(args.precision, wl.cells[0].shape, min_om)
     if args.precond or args.block >= 2:
         alg_pp = host_driven_bytes(args.precond, args.block, wl.cells[0].shape)
     alg = alg_pp * pit
@@ -508,7 +547,7 @@ def run_energy(args):
         timing = ("forward wall time (cells one after another)" if args.cells_sequential
                   else "forward wall time (concurrent cells)")
     traffic, tb = cocg_traffic(wl.name, args.precision, pit / max(1, launches))
-    kernel = "cocg_wg (batched COCG, one workgroup per system)"
+    kernel = kernel_name(args.precision, wl.cells[0].shape, min_om)
 
     def converged(iters):
         return subspace_converged(iters, opts["ec_tol"], opts["subspace_iters"])
@@ -575,7 +614,7 @@ def run_energy(args):
             "E_c": s2["E"], "subspace_iters": s2["iters"], "converged": converged(s2["iters"]),
             "time_to_ec_label": label(s2["iters"]),
             "E_c_rel_diff": [abs(a - b) / abs(b) for a, b in zip(s2["E"], steps[-1]["E"])],
-            "cocg_alg_GBs": ALG_BYTES[other] * s2["point_iters"] / (s2["cocg_ms"] * 1e-3) / 1e9,
+            "cocg_alg_GBs": alg_bytes(other, wl.cells[0].shape, min_om) * s2["point_iters"] / (s2["cocg_ms"] * 1e-3) / 1e9,
             "time_to_ec_ratio_vs_main": s2["fwd_s"] / out["time_to_ec_s"],
         }
         print("[bench] compare %s: %.2f s fwd, %.2f applies/s, E_c %s" % (

@@ -660,7 +660,7 @@ RcocgLaunch real_launch(const rpa_cell* cell, const Grid& g, const Opts& o, cons
 }
 
 // RPA_MIXED at and above mixed_min_omega: where the real-form FP64 kernel has a launch shape it
-// solves faster than the complex64 one (48^3, omega 49.4, 16384 systems: 1.2 us per
+// solves faster than the complex64 one (48^3, omega 49.4, 16384 systems: 1.05 us per
 // system-iteration against 2.1) and takes the place of the complex64 recurrences; their float64
 // refinement stays as one float64 residual b - A x per system, on which the tolerance is tested.
 // mixed_min_omega = 0 asks for complex64 at every frequency.

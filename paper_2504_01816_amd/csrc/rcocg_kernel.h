@@ -567,7 +567,7 @@ void rcocg_wg(Args a) {
 // system per workgroup: the real and the imaginary part of x are marched one after the other on
 // the solver's planes (the second finds x in the caches).  Norms mode (rout null): status 0
 // becomes 1 where |r| > tol |b|, refinements is 1, b2 = |b|^2.  Else r is stored, interleaved.
-// 48^3, 16384 systems: 23 ms beside 385 for the shortest solves (21 iterations); plain gathers of
+// 48^3, 16384 systems: 23 ms beside 339 for the shortest solves (21 iterations); plain gathers of
 // the 37 points took 60.
 struct CheckArgs {
     int n0, n1, n2, P;
