@@ -1,16 +1,17 @@
 // Kronecker transforms of whole vectors in three passes, for grids whose axes have at most
 // kKronAxis points: x and y of a z-plane forward; z forward, the diagonal scale and z back on 64
 // columns; x and y back.  They serve nu^{1/2} and nu (real vectors) and the shifted-Laplacian
-// preconditioner (complex vectors as pairs of real ones).  A pass moves 16 B per point and does
-// 4 n flops per point and product, so memory bounds it (48^3, 256 vectors: 97 us at 4.67 TB/s, 75 us
-// of FP64 MFMA at 72.5 TFLOP/s), if neither latency shows.  Therefore a workgroup has one wave per
+// preconditioner (complex vectors as pairs of real ones).  A pass moves 16 B per point and does two
+// products of 2 n flops per point, so memory bounds it (48^3, 256 vectors: 97 us at 4.67 TB/s, 75 us
+// of FP64 MFMA at 72.5 TFLOP/s), if no latency shows.  Therefore a workgroup has one wave per
 // 16 x 16 tile of its plane (or of its 64 columns): each wave keeps the two factors of its tile in
 // registers for all planes it takes, only the data goes through LDS (two buffers, two barriers per
 // plane), the next plane is loaded behind the products, and no branch lies between loads and stores.
-// Measured, 48^3, 256 vectors: 149, 117 and 142 us; with four waves a workgroup and the factors in
-// LDS, 270 us each (9 tiles over 4 waves, 2 workgroups per CU); with branches around the stores, 164,
-// 128 and 158 (the wait for the loads waits for the stores).  With 9 waves the registers allow two
-// workgroups per CU, which is what keeps the x-y passes from 97 us.
+// Measured, 48^3, 256 vectors, traced, the mean of four calls with the cold first: 149, 117 and
+// 142 us; with four waves a workgroup and the factors in LDS, 270 us each (9 tiles over 4 waves, 2
+// workgroups per CU); with branches around the stores, 164, 128 and 158 (the wait for the loads
+// waits for the stores).  With 9 waves the registers allow two workgroups per CU, which is what
+// keeps the x-y passes from 97 us.
 #include <algorithm>
 #include <type_traits>
 
