@@ -80,6 +80,25 @@ struct Args {
     int periodic;
 };
 
+// Ragged, periodic sweeps: the reads of v past the top (plane z + 7 - n2 of v in step z, from
+// z = n2 - 7 on) go to rows that other threads stored in step z + 7 - n2.  Whether step z starts
+// with the barrier that orders them.  It stands in front of the step's own stores, so the one in
+// step n2 - 7 covers planes 0 .. n2 - 8: all six from n2 = 13 on; n2 = 12 needs another one for
+// plane 5, which step n2 - 2 reads.
+__host__ __device__ constexpr bool wrap_barrier(int n2, int z) {
+    return z == n2 - 7 || (n2 == 12 && z == n2 - 2);
+}
+// Every such read has a barrier after its store's step and no later than its own.
+constexpr bool wrap_ordered(int n2) {
+    for (int z = n2 - 7; z <= n2 - 2; ++z) {
+        bool ok = false;
+        for (int b = z + 7 - n2 + 1; b <= z; ++b) ok = ok || wrap_barrier(n2, b);
+        if (!ok) return false;
+    }
+    return true;
+}
+static_assert(wrap_ordered(12) && wrap_ordered(13) && wrap_ordered(14) && wrap_ordered(48), "");
+
 __device__ __forceinline__ void global_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_barrier();
@@ -284,8 +303,8 @@ __device__ __forceinline__ void sweep(const Args& a, const Rows<C>& rw, double* 
             }
         }
         du = du + 1 == kDelay ? 0 : du + 1;
-        // ragged: the fetches past the top read v of rows that other threads stored
-        if (RAG && zo + Z + 6 <= n2 && zo + 2 * Z + 6 > n2) global_barrier();
+        static_assert(!RAG || Z == 1, "wrap_barrier counts single planes");
+        if (RAG && per && wrap_barrier(n2, zo)) global_barrier();
         if (stp + 1 < nsteps) fetch(zo + Z);
         double* L = planes + (a.nbuf == 2 ? (stp & 1) : 0) * Z * PL;
 #pragma unroll

@@ -184,3 +184,18 @@ def test_streaming_iteration_caps(shape, cap):
     # over the tiles of 64 systems), so the right-hand sides are the same bits too
     if c.nd // 128 <= 2048 // 16:
         assert np.array_equal(many[:2], few) and np.array_equal(many[-2:], few)
+
+
+@pytest.mark.parametrize("shape", [(35, 37, 12), (47, 46, 12), (41, 25, 12)])
+def test_ragged_periodic_grids_of_the_smallest_height(shape):
+    # rows that do not divide by the rows per thread, n2 = 12: the last plane that a sweep reads past
+    # the periodic top is stored after the first of its two barriers
+    say("ragged, n2 = 12", shape)
+    c = make(shape, 2, 17)
+    X = np.random.default_rng(18).standard_normal((2, c.nd))
+    for omega in (0.1, 2.0):
+        ref, iters, _ = ochi0.chi0_apply(X.T, c.vloc, c.psi.T, c.eps, omega, shape, c.h, 1e-12, 5000)
+        for precision in (0, 1):
+            out, rc, st = chi0(c, X, omega, 1e-12, precision=precision)
+            # two FP64 solvers that meet a residual of 1e-12 differ by cond(A) 1e-12 <= 1e-9 here
+            assert rc == 0 and rel(out.T, ref) < 1e-9, (omega, precision, rel(out.T, ref))
