@@ -649,6 +649,7 @@ RcocgLaunch real_launch(const rpa_cell* cell, const Grid& g, const Opts& o, cons
     R.counter = b.order + n;
     R.tol = o.cocg_tol;
     R.max_iter = o.cocg_max_iter;
+    R.tiny_status = 2;              // a breakdown, as in complex COCG, whose p^T A p underflows
     R.rhs = b.rhs;
     R.x = b.x;
     R.pool = b.pool;
@@ -765,6 +766,8 @@ int solve_chunk(const rpa_cell* cell, const Grid& g, const Opts& o, const Chi0Bu
     if (real_form) {
         RcocgLaunch R = real_launch(cell, g, o, b, ns * nv);
         R.x_complex = x_complex || checked;
+        // in complex64 such a right-hand side rounds to zero, and x = 0 solves it
+        if (checked) R.tiny_status = 0;
         hipEvent_t e0, e1;
         RPA_CHECK(timer_events(&e0, &e1));
         RPA_HIP(hipEventRecord(e0, s));

@@ -160,6 +160,7 @@ struct RcocgLaunch {
     int* counter;           // device, 0
     double tol;
     int max_iter;
+    int tiny_status;        // of a right-hand side whose residuals' squares are no normal numbers
     const double* rhs;      // nsys x N_d real
     void* x;                // nsys x N_d real (complex if x_complex)
     bool x_complex;

@@ -173,6 +173,7 @@ hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
     a.counter = L.counter;
     a.tol2 = L.tol * L.tol;
     a.max_iter = L.max_iter;
+    a.tiny_status = L.tiny_status;
     a.nd = L.g.nd();
     a.rhs = L.rhs;
     a.x = L.x;

@@ -66,6 +66,7 @@ struct Args {
     int* counter;          // next position in order (0 before the launch)
     double tol2;
     int max_iter;
+    int tiny_status;       // status of a right-hand side that is too small to solve for (x = 0)
     int64_t nd;
     const double* rhs;     // system-major, N_d real each
     void* x;               // system-major: N_d real (XS = double) or complex (double2)
@@ -353,25 +354,35 @@ struct Coef {
     double lr, li, er, ei;
 };
 
+// A right-hand side so small that squares of residuals between |b| and the tolerance (or, for
+// tighter tolerances, rounding) are no normal numbers, and no test of them means anything.
+__device__ __forceinline__ bool too_small(double bb, double tol2) {
+    return bb * fmax(tol2, 1e-32) < 2.2250738585072014e-308;
+}
+
 // The scalars of one solve: what the reductions of a sweep turn into.  Every value is uniform over
 // the workgroup (wg_reduce), and every thread computes all of them.
 struct Recurrence {
     double omega, tol2;
-    int max_iter;
+    int max_iter, tiny_status;
     double sigma = 0.0, delta = 0.0, beta = 0.0, ibeta = 1.0;
     double sc = 1.0, bn = 0.0, ibn = 0.0, tgt2 = 0.0;        // sc: 1 / |b| while v_1 stands for b
     double zr = 0.0, zi = 0.0, ir = 0.0, ii = 0.0, b2 = 0.0;  // zeta, 1 / d, beta^2
     int it = 0, stat = 0;
     bool done = false;
 
-    __device__ __forceinline__ Recurrence(double w, double t2, int mi)
-        : omega(w), tol2(t2), max_iter(mi) {}
+    __device__ __forceinline__ Recurrence(double w, const Args& a)
+        : omega(w), tol2(a.tol2), max_iter(a.max_iter), tiny_status(a.tiny_status) {}
     __device__ __forceinline__ double cp() const { return it == 0 ? 0.0 : beta * sc; }
     // acc = (v.w, w.w, v.v) of the sweep.  The first one is on b itself: its sums are scaled to
-    // v_1 = b / |b|.  False for a zero right-hand side.
+    // v_1 = b / |b|.  False for a right-hand side that is zero or too small.
     __device__ __forceinline__ bool norms(double (&acc)[3]) {
         if (it == 0) {
             if (!(acc[2] > 0.0)) return false;
+            if (too_small(acc[2], tol2)) {
+                stat = tiny_status;
+                return false;
+            }
             tgt2 = uniform(tol2 * acc[2]);
             bn = uniform(sqrt(acc[2]));
             ibn = uniform(1.0 / bn);
@@ -518,7 +529,7 @@ void rcocg_wg(Args a) {
         const double diag = a.cw[0] - a.eps[sys % a.ns];
         const double* b = a.rhs + int64_t(sys) * a.nd;
         XS* x = reinterpret_cast<XS*>(a.x) + int64_t(sys) * a.nd;
-        Recurrence rc(omega, a.tol2, a.max_iter);
+        Recurrence rc(omega, a);
         int slot = 0;                                 // rc.it mod ring
         bool px_first = true, carry = false, redo = false;
         while (!rc.done) {
@@ -535,7 +546,7 @@ void rcocg_wg(Args a) {
                              c2, rc.cp(), vnew, w, Q, carry, acc, delay);
             if (RAG) global_barrier();           // w of rows that other threads stored
             wg_reduce<3>(acc, red);
-            if (!rc.norms(acc)) break;           // zero right-hand side
+            if (!rc.norms(acc)) break;           // zero or too small a right-hand side
             if (rc.cancels(acc) && !redo) {
                 // cancellation: once more with sigma = alpha
                 rc.shift(acc);
@@ -566,7 +577,7 @@ void rcocg_wg(Args a) {
             }
         }
         if (rc.it == 0) {
-            // zero right-hand side: x = 0 (not a number where b is not finite)
+            // nothing solved: x = 0 (not a number where b is not finite)
             for (unsigned i = tid; i < unsigned(a.nd); i += BS) {
                 const double v = 0.0 * ld(b, i);
                 if constexpr (std::is_same<XS, double>::value) st(x, i, v);
@@ -679,7 +690,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64, BSMAX))) void check_wg
     if (rout) return;
     wg_reduce<3>(acc, red);
     if (threadIdx.x == 0) {
-        if (a.status[sys] == 0 && !(acc[0] <= a.tol2 * acc[1])) a.status[sys] = 1;
+        if (a.status[sys] == 0 && !(acc[0] <= a.tol2 * acc[1]) && !too_small(acc[1], a.tol2))
+            a.status[sys] = 1;
         if (a.refinements) a.refinements[sys] = 1;
         a.b2[sys] = acc[1];
     }

@@ -215,7 +215,7 @@ __device__ __forceinline__ void finish(const Args& a, int sys, const Recurrence&
     }
 }
 
-// Zero right-hand side: x = 0 (not a number where b is not finite).
+// Nothing solved: x = 0 (not a number where b is not finite).
 __device__ __forceinline__ void zero_x(const Args& a, int sys, const double* b) {
     for (unsigned i = threadIdx.x; i < unsigned(a.nd); i += blockDim.x) {
         const double v = 0.0 * ld(b, i);
@@ -239,7 +239,7 @@ void full_wg(Args a) {
     for (int sys; (sys = next_system(a, next)) >= 0;) {
         const double* b = a.rhs + int64_t(sys) * a.nd;
         const double diag = a.cw[0] - a.eps[sys % a.ns];
-        Recurrence rc(a.omega_v[sys / a.ns], a.tol2, a.max_iter);
+        Recurrence rc(a.omega_v[sys / a.ns], a);
         double V[NZ], W[NZ], PR[NZ], PI[NZ], X[NZ];
 #pragma unroll
         for (int z = 0; z < NZ; ++z) {
@@ -252,7 +252,7 @@ void full_wg(Args a) {
             double acc[3] = {0.0, 0.0, 0.0};
             sweep<NZ, false>(a, c, planes, diag - rc.sigma, rc.cp(), nullptr, V, W, first, acc);
             wg_reduce<3>(acc, red);
-            if (!rc.norms(acc)) break;                // zero right-hand side
+            if (!rc.norms(acc)) break;                // zero or too small a right-hand side
             if (rc.cancels(acc)) {
                 const double dl = rc.shift(acc);
                 double ac2[3] = {0.0, 0.0, 0.0};
@@ -392,7 +392,7 @@ void ring_wg(Args a) {
         const double* b = a.rhs + int64_t(sys) * a.nd;
         X* x = reinterpret_cast<X*>(a.x) + int64_t(sys) * a.nd;
         const double diag = a.cw[0] - a.eps[sys % a.ns];
-        Recurrence rc(a.omega_v[sys / a.ns], a.tol2, a.max_iter);
+        Recurrence rc(a.omega_v[sys / a.ns], a);
         int slot = 0, half = 0;                         // fill of the half in use
         bool none = true;                               // no half folded yet
         if (!folds) {
@@ -410,7 +410,7 @@ void ring_wg(Args a) {
                 sweep<NZ, true>(a, c, planes, diag - rc.sigma, rc.cp(), ring + (half * M + slot) * a.nd,
                                 V, W, first, acc);
                 wg_reduce<3>(acc, red);
-                if (!rc.norms(acc)) break;            // zero right-hand side
+                if (!rc.norms(acc)) break;            // zero or too small a right-hand side
                 if (rc.cancels(acc)) {
                     const double dl = rc.shift(acc);
                     double ac2[3] = {0.0, 0.0, 0.0};

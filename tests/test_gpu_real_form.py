@@ -199,3 +199,21 @@ def test_ragged_periodic_grids_of_the_smallest_height(shape):
             out, rc, st = chi0(c, X, omega, 1e-12, precision=precision)
             # two FP64 solvers that meet a residual of 1e-12 differ by cond(A) 1e-12 <= 1e-9 here
             assert rc == 0 and rel(out.T, ref) < 1e-9, (omega, precision, rel(out.T, ref))
+
+
+@pytest.mark.parametrize("shape", [(12, 13, 14), (20, 20, 21), (12, 12, 33), (35, 37, 12)])
+def test_tiny_right_hand_sides_are_solved_or_reported(shape):
+    # scaled by 1e-100 the solves are those of the unscaled block; by 1e-160 the squares of the
+    # residuals are no normal numbers: a breakdown, or zero where complex64 stands for the block
+    say("tiny right-hand sides", shape)
+    c = make(shape, 2, 19)
+    X = np.random.default_rng(20).standard_normal((2, c.nd))
+    ref, rc, st = chi0(c, X, 0.5, 1e-10)
+    out, rc2, st2 = chi0(c, X * 1e-100, 0.5, 1e-10)
+    assert rc == 0 and rc2 == 0 and abs(st2["cocg_iters_total"] - st["cocg_iters_total"]) <= 4
+    assert rel(out * 1e100, ref) < 1e-8              # both meet 1e-10, cond(A) times that
+    for omega, precision in ((0.5, 0), (0.1, 1)):
+        with pytest.raises(RuntimeError, match="breakdown"):
+            chi0(c, X * 1e-160, omega, 1e-10, precision=precision)
+    out, rc, st = chi0(c, X * 1e-160, 0.5, 1e-10, precision=1)
+    assert rc == 0 and np.all(out == 0.0) and st["fp64_fallbacks"] == 0
