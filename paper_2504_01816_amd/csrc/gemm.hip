@@ -588,7 +588,7 @@ hipError_t launch_kron_apply(const Grid& g, int power, int nvec, const double* i
     // vectors 820 -> 372 us, 64^3, 16 vectors 156 -> 109, 24^3, 64 vectors 88 -> 37, 12^3, one vector
     // 45 -> 27 (whole calls, with the bases)
     if (kron_fused_fits(g))
-        return launch_kron_fused(g, power, nvec, in, out, Ux, Uy, Uz, kx, ky, kz, s);
+        return launch_kron_fused(g, power, nvec, in, out, tmp, Ux, Uy, Uz, kx, ky, kz, s);
     // keep every launch within the grid limits: gridDim.z = n2 * chunk (y pass) and
     // gridDim.y = n1 * n2 * chunk / 64 (x pass) must stay below 65536
     const int64_t lim_y = 65535 / g.n2;

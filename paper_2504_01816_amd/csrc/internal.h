@@ -79,10 +79,10 @@ hipError_t launch_kron_apply(const Grid& g, int power, int nvec, const double* i
                              const double* kx, const double* ky, const double* kz,
                              hipStream_t s);
 // The same and the preconditioner below in three fused passes (kron.hip), for axes that fit;
-// in == out is allowed.
+// in and out may be the same or overlap (tmp, a whole block, is used only then).
 bool kron_fused_fits(const Grid& g);
 hipError_t launch_kron_fused(const Grid& g, int power, int nvec, const double* in, double* out,
-                             const double* Ux, const double* Uy, const double* Uz, const double* kx,
+                             double* tmp, const double* Ux, const double* Uy, const double* Uz, const double* kx,
                              const double* ky, const double* kz, hipStream_t s);
 hipError_t launch_kron_fused_precond(const Grid& g, int nsys, const double* in, double* out,
                                      const double* Ux, const double* Uy, const double* Uz,

@@ -300,22 +300,23 @@ hipError_t with_steps(int n, F f) {
     return f(std::integral_constant<int, 16>{});
 }
 
+// mid: where the transform lies between the passes; out, or a block apart from both.
 template <bool PRE>
-hipError_t run(const Grid& g, int nvec, const double* in, double* out, const double* Ux,
-               const double* Uy, const double* Uz, const double* kx, const double* ky,
-               const double* kz, int power, const double2* kshift, hipStream_t s) {
+hipError_t run(const Grid& g, int nvec, const double* in, double* mid, double* out,
+               const double* Ux, const double* Uy, const double* Uz, const double* kx,
+               const double* ky, const double* kz, int power, const double2* kshift, hipStream_t s) {
     const int64_t planes = int64_t(g.n2) * nvec * (PRE ? 2 : 1);
     const int nxy = std::max(g.n0, g.n1);
     hipError_t e = with_steps(nxy, [&](auto K) {
-        return run_xy<decltype(K)::value, false>(g, planes, in, out, Ux, Uy, s);
+        return run_xy<decltype(K)::value, false>(g, planes, in, mid, Ux, Uy, s);
     });
     if (e != hipSuccess) return e;
     e = with_steps(g.n2, [&](auto K) {
-        return run_z<decltype(K)::value, PRE>(g, nvec, out, Uz, kx, ky, kz, power, kshift, s);
+        return run_z<decltype(K)::value, PRE>(g, nvec, mid, Uz, kx, ky, kz, power, kshift, s);
     });
     if (e != hipSuccess) return e;
     return with_steps(nxy, [&](auto K) {
-        return run_xy<decltype(K)::value, true>(g, planes, out, out, Ux, Uy, s);
+        return run_xy<decltype(K)::value, true>(g, planes, mid, out, Ux, Uy, s);
     });
 }
 
@@ -323,11 +324,16 @@ hipError_t run(const Grid& g, int nvec, const double* in, double* out, const dou
 
 bool kron_fused_fits(const Grid& g) { return std::max(g.n0, std::max(g.n1, g.n2)) <= kKronAxis; }
 
+// The first pass reads planes of `in` in any order while it writes others: blocks that overlap
+// without being the same go through tmp, so that all of `in` is read before `out` is written.
 hipError_t launch_kron_fused(const Grid& g, int power, int nvec, const double* in, double* out,
-                             const double* Ux, const double* Uy, const double* Uz, const double* kx,
+                             double* tmp, const double* Ux, const double* Uy, const double* Uz, const double* kx,
                              const double* ky, const double* kz, hipStream_t s) {
     if (nvec <= 0) return hipSuccess;
-    return run<false>(g, nvec, in, out, Ux, Uy, Uz, kx, ky, kz, power, nullptr, s);
+    const size_t bytes = size_t(g.nd()) * nvec * sizeof(double);
+    const uintptr_t a = reinterpret_cast<uintptr_t>(in), b = reinterpret_cast<uintptr_t>(out);
+    double* mid = a != b && a < b + bytes && b < a + bytes ? tmp : out;
+    return run<false>(g, nvec, in, mid, out, Ux, Uy, Uz, kx, ky, kz, power, nullptr, s);
 }
 
 hipError_t launch_kron_fused_precond(const Grid& g, int nsys, const double* in, double* out,
@@ -335,7 +341,7 @@ hipError_t launch_kron_fused_precond(const Grid& g, int nsys, const double* in, 
                                      const double* kx, const double* ky, const double* kz,
                                      const double2* kshift, hipStream_t s) {
     if (nsys <= 0) return hipSuccess;
-    return run<true>(g, nsys, in, out, Ux, Uy, Uz, kx, ky, kz, 0, kshift, s);
+    return run<true>(g, nsys, in, out, out, Ux, Uy, Uz, kx, ky, kz, 0, kshift, s);
 }
 
 }  // namespace rpa

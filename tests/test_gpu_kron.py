@@ -56,3 +56,19 @@ def test_preconditioner_axes(shape, bc):
     assert rc == 0
     assert rel(out.T, ref) < 1e-9
     assert abs(st["cocg_iters_total"] - int(it.sum())) <= it.size
+
+
+@pytest.mark.parametrize("fn", [api.rpa_apply_coulomb, api.rpa_apply_coulomb_noalloc])
+@pytest.mark.parametrize("shape,nvec", [((12, 13, 14), 5), ((24, 25, 12), 40), ((12, 66, 12), 4)])
+def test_coulomb_blocks_that_overlap(shape, nvec, fn):
+    # the output block starts one vector, or one point, behind or in front of the input block
+    c = synth.uniform_cell(shape, 0.45, 0.0)
+    dc, n = api.device_cell(c, DEV), nvec * c.nd
+    X = torch.tensor(np.random.default_rng(6).standard_normal((nvec, c.nd)), device=DEV)
+    ref = fn(dc, X, 2)
+    for shift in (c.nd, 1, -1, -c.nd):
+        buf = torch.zeros(n + abs(shift), dtype=torch.float64, device=DEV)
+        a, b = max(0, -shift), max(0, shift)
+        buf[a:a + n] = X.reshape(-1)
+        out = fn(dc, buf[a:a + n].view(nvec, c.nd), 2, out=buf[b:b + n].view(nvec, c.nd))
+        assert torch.equal(out, ref), shift
