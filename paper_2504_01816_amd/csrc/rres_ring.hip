@@ -7,7 +7,8 @@ namespace rres {
 // Four registers per point of the column (v, w) and about fifty more: 168 per thread (12 waves) hold
 // 26 points, 256 (8 waves) 32.
 KernelFn ring_variant(int nz, bool xc, int half) {
-    if (half == kRingHalfMin && !xc) return nullptr;
+    // short halves only for complex solutions of the columns whose real ones full_wg takes
+    if (half == kRingHalfMin && (!xc || nz > 20)) return nullptr;
 #define RPA_S(N)                                                               \
     case N: return half == kRingHalfMin ? ring_wg<N, 768, 3, kRingHalfMin, true> \
                  : xc ? ring_wg<N, 768, 3, kRing, true> : ring_wg<N, 768, 3, kRing, false>;
