@@ -189,6 +189,10 @@ int rpa_default_options(rpa_options* opt);
  *           workspace holds every frequency's block; ignored otherwise)
  *   opt     options (NULL = defaults)
  *   bytes   host out
+ * Calls that solve few systems (about 1000 or fewer) ask for more than the state named at
+ * max_systems, for a longer ring of basis vectors per system.  They also accept a workspace
+ * without it, down to that state and the blocks of the driver, and then run with a shorter
+ * ring: slower, equal to rounding.
  */
 int rpa_workspace_size(int32_t op, int32_t ncell, const rpa_cell* cells, const int32_t* nvec,
                        int32_t nfreq, const rpa_options* opt, size_t* bytes);

@@ -76,6 +76,7 @@ struct Opts {
                                  // below: the library default, or a cell's share of it)
     bool precond = false;        // RPA_FLAG_PRECOND
     int block = 0;               // cocg_block: block COCG width (0, 1: off)
+    bool lean = false;           // the caller's workspace holds only the least state (fit_ws)
     // the host-driven solver (split vectors): preconditioned or block COCG
     bool host_driven() const { return precond || block >= 2; }
 };
@@ -175,6 +176,17 @@ int check_solver_geometry(const rpa_cell* c, const Opts& o) {
     return RPA_OK;
 }
 
+// Small launches ask for more than the least state: a longer ring of basis vectors per system and
+// more parts in the split sums.  A workspace that holds only the least still works, with a ring of
+// at least two vectors.  need(o): bytes with options o; on return o says which of the two fits.
+template <typename F>
+size_t fit_ws(size_t ws_bytes, Opts* o, F need) {
+    const size_t full = need(*o);
+    if (ws_bytes >= full) return full;
+    o->lean = true;
+    return need(*o);
+}
+
 int check_ws(void* ws, size_t ws_bytes, size_t need) {
     if (need == 0) return RPA_OK;
     if (!ws) return fail(RPA_EWORKSPACE, "workspace pointer is NULL");
@@ -218,7 +230,7 @@ struct Chi0Buf {
     float* vloc32;  // mixed only: V_loc in float32 for the complex64 sweeps
     int *iters, *status, *refine;
     double* omega_v;  // per trial vector of a chunk: its frequency
-    int* order;       // per system of a chunk: dispatch order
+    int* order;       // per system of a chunk: dispatch order; then a counter (in part's place)
     // real-form COCG (FP64 solves on grids with a launch shape): the right-hand sides and the
     // solver's state pool, both inside the buffers above
     bool real_form;
@@ -297,13 +309,13 @@ int chunk_vectors(int64_t nd, int ns, int nvec, const Opts& o) {
 // With at least 1024 (512 in the Gram products) small problems ran on a handful of workgroups:
 // projector coefficients 112.6 -> 13.1 us at 12^3, 74 -> 44 us at 24^3; Gram 33.7 -> 11.2 us at 20^3,
 // N_r 32 (the sum of the parts included in none of them).
-int grid_split(int64_t nd, int tiles) {
+int grid_split(int64_t nd, int tiles, int least) {
     const int sp = std::max(1, 2048 / std::max(1, tiles));
-    return int(std::min<int64_t>(sp, std::max<int64_t>(1, nd / 128)));
+    return int(std::min<int64_t>(sp, std::max<int64_t>(1, nd / least)));
 }
 
-int coeff_split(int64_t nd, int ns, int S) {
-    return grid_split(nd, ((ns + 63) / 64) * ((S + 63) / 64));
+int coeff_split(int64_t nd, int ns, int S, const Opts& o) {
+    return grid_split(nd, ((ns + 63) / 64) * ((S + 63) / 64), o.lean ? 1024 : 128);
 }
 
 void carve_chi0(Carver& cv, const Grid& g, int ns, int nvec, const Opts& o, bool x_complex,
@@ -311,7 +323,7 @@ void carve_chi0(Carver& cv, const Grid& g, int ns, int nvec, const Opts& o, bool
     b.chunk = chunk_vectors(g.nd(), ns, nvec, o);
     const int S = ns * b.chunk;
     const int64_t nd = g.nd();
-    b.nsplit = coeff_split(nd, ns, S);
+    b.nsplit = coeff_split(nd, ns, S, o);
     b.mixed = (o.precision == RPA_MIXED);
     b.precond = o.host_driven();
     b.kron = o.precond;
@@ -323,35 +335,40 @@ void carve_chi0(Carver& cv, const Grid& g, int ns, int nvec, const Opts& o, bool
     b.eps = cv.take<double>(ns);
     b.coeff = cv.take<double>(size_t(ns) * S);
     b.part = cv.take<double>(size_t(b.nsplit) * ns * S);
+    // the dispatch list and the real-form kernel's counter (S + 1 ints) take the place of the parts
+    // once these are summed
+    b.order = reinterpret_cast<int*>(b.part);
     // mixed: r, p_a, p_b, x_lo (complex64) back to back, so that [r | p_a] and [p_b | x_lo]
     // each hold S x N_d complex128 values for the FP64 continuation of capped systems
     b.r = cv.take<char>(size_t(S) * nd * cplx);
+    const size_t rhs_end = cv.used - size_t(S) * nd * (cplx - 8);
     b.pa = cv.take<char>(size_t(S) * nd * cplx);
     b.pb = cv.take<char>(size_t(S) * nd * cplx);
     b.xlo = b.mixed ? cv.take<char>(size_t(S) * nd * 8) : nullptr;
+    b.rhi = b.mixed ? cv.take<double>(2 * size_t(S) * nd) : nullptr;
     // Real-form COCG keeps its right-hand sides in the first 8 B per point and system of r and
-    // its pool of slots behind them, up to the end of the direction vectors; launches of few
-    // systems get the rest of their slots here.
+    // its pool of slots behind them, up to the end of the buffers above: 40 B or more per point and
+    // system, which is a ring of two vectors, w and p for each.  Launches of few systems get the
+    // rest of their slots here, unless the workspace is lean.
     b.real_form = !b.precond && rcocg_fits(g);
     b.rhs = static_cast<double*>(b.r);
     b.pool = nullptr;
     b.pool_bytes = 0;
     if (b.real_form) {
-        const size_t first = (cv.used - size_t(S) * nd * (b.mixed ? 24 : 40)) / 256 * 256 + 256;
-        b.pool_bytes = rcocg_pool_bytes(g, S);
+        // (an odd S N_d leaves a gap of 8 B behind rhs, and one of 8 B or more behind r to pay it)
+        const size_t first = (rhs_end + (o.lean ? 15 : 255)) / (o.lean ? 16 : 256) * (o.lean ? 16 : 256);
+        if (!o.lean) b.pool_bytes = rcocg_pool_bytes(g, S);
         if (first + b.pool_bytes > cv.used) cv.take<char>(first + b.pool_bytes - cv.used);
         else b.pool_bytes = cv.used - first;         // a longer ring where the room is there
         if (cv.base) b.pool = reinterpret_cast<double*>(cv.base + first);
     }
     b.x = cv.take<char>(size_t(S) * nd * (b.x_complex ? 16 : 8));
-    b.rhi = b.mixed ? cv.take<double>(2 * size_t(S) * nd) : nullptr;
     b.b2 = b.mixed ? cv.take<double>(S) : nullptr;
     b.vloc32 = b.mixed ? cv.take<float>(size_t(nd)) : nullptr;
     b.iters = cv.take<int>(S);
     b.status = cv.take<int>(S);
     b.refine = cv.take<int>(S);
     b.omega_v = cv.take<double>(b.chunk);
-    b.order = cv.take<int>(size_t(S) + 1);
     b.dbuf = with_d ? cv.take<double2>(size_t(ns) * S) : nullptr;
     if (b.precond) {
         const size_t blk = 2 * size_t(S) * nd;
@@ -386,8 +403,8 @@ void carve_chi0(Carver& cv, const Grid& g, int ns, int nvec, const Opts& o, bool
     }
 }
 
-int gram_split(int64_t nd, int m) {
-    return grid_split(nd, ((m + 63) / 64) * ((m + 63) / 64));
+int gram_split(int64_t nd, int m, const Opts& o) {
+    return grid_split(nd, ((m + 63) / 64) * ((m + 63) / 64), o.lean ? 512 : 128);
 }
 
 struct SubBuf {
@@ -408,12 +425,12 @@ void carve_sub(Carver& cv, const Grid& g, int ns, int nr, const Opts& o, SubBuf&
     b.M = cv.take<double>(sq);
     b.L = cv.take<double>(sq);
     b.T = cv.take<double>(sq);
-    b.gsplit = gram_split(g.nd(), nr);
+    b.gsplit = gram_split(g.nd(), nr, o);
     b.part = cv.take<double>(size_t(b.gsplit) * sq);
     b.ework = cv.take<double>(2 * sq);
     b.escal = cv.take<double>(8);
     b.eigw = cv.take<double>(nr);
-    b.eigwork = cv.take<double>(2 * sq + 8 * size_t(nr));
+    b.eigwork = cv.take<double>(2 * sq);
     b.info = cv.take<int>(8);
 }
 
@@ -453,7 +470,7 @@ void carve_batch(Carver& cv, const Grid& g, int ns, int nr, int nf, const Opts& 
     b.M = cv.take<double>(sq * nf);
     b.L = cv.take<double>(sq * nf);
     b.T = cv.take<double>(sq * nf);
-    b.gsplit = gram_split(g.nd(), nr);
+    b.gsplit = gram_split(g.nd(), nr, o);
     b.part = cv.take<double>(size_t(b.gsplit) * sq);
     b.ework = cv.take<double>(2 * sq);
     b.escal = cv.take<double>(8 * size_t(nf));
@@ -473,7 +490,7 @@ void carve_back(Carver& cv, const Grid& g, int ns, int nr, const Opts& o, BackBu
     b.U = cv.take<double>(blk);
     b.Y = cv.take<double>(sq);
     b.mu = cv.take<double>(nr);
-    b.eigwork = cv.take<double>(2 * sq + 8 * size_t(nr));
+    b.eigwork = cv.take<double>(2 * sq);
     b.coefk = cv.take<double>(nr);
 }
 
@@ -860,8 +877,9 @@ int continue_capped(const rpa_cell* cell, const Grid& g, const Opts& o, const Ch
         if (h.st[i] != 1 && h.st[i] != 2) continue;
         (real_form && !checked && h.st[i] == 2 && h.it[i] == 1 ? fresh : capped).push_back(i);
     }
+    // the capped ones first: the pool of the real-form solves reaches into r_hi
     for (int pass = 0; pass < 2; ++pass) {
-        std::vector<int>& list = pass == 0 ? fresh : capped;
+        std::vector<int>& list = pass == 0 ? capped : fresh;
         if (list.empty()) continue;
         const int n = int(list.size());
         list.push_back(0);             // the real-form kernel's position counter
@@ -870,7 +888,7 @@ int continue_capped(const rpa_cell* cell, const Grid& g, const Opts& o, const Ch
         list.pop_back();
         hipEvent_t e0, e1;
         RPA_CHECK(timer_events(&e0, &e1));
-        if (pass == 0) {
+        if (pass == 1) {
             RPA_HIP(launch_real_part(int64_t(S) * g.nd(), b.rhi, b.rhs, s));
             RcocgLaunch R = real_launch(cell, g, o, b, n);
             R.x_complex = true;
@@ -1500,10 +1518,12 @@ int rpa_apply_chi0(const rpa_cell* cell, double omega, int32_t nvec, const doubl
     RPA_CHECK(read_opts(opt, &o));
     RPA_CHECK(check_solver_geometry(cell, o));
     const Grid g = grid_of(cell);
-    Carver dry;
     Chi0Buf b;
-    carve_chi0(dry, g, cell->n_occ, nvec, o, false, false, b);
-    RPA_CHECK(check_ws(ws, ws_bytes, dry.used));
+    RPA_CHECK(check_ws(ws, ws_bytes, fit_ws(ws_bytes, &o, [&](const Opts& p) {
+        Carver dry;
+        carve_chi0(dry, g, cell->n_occ, nvec, p, false, false, b);
+        return dry.used;
+    })));
     Carver cv{static_cast<char*>(ws), 0};
     carve_chi0(cv, g, cell->n_occ, nvec, o, false, false, b);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1530,10 +1550,12 @@ int rpa_subspace_iter(const rpa_cell* cell, double omega, double weight, int32_t
     Opts o;
     RPA_CHECK(read_opts(opt, &o));
     RPA_CHECK(check_solver_geometry(cell, o));
-    Carver dry;
     SubBuf b;
-    carve_sub(dry, g, cell->n_occ, nr, o, b);
-    RPA_CHECK(check_ws(ws, ws_bytes, dry.used));
+    RPA_CHECK(check_ws(ws, ws_bytes, fit_ws(ws_bytes, &o, [&](const Opts& p) {
+        Carver dry;
+        carve_sub(dry, g, cell->n_occ, nr, p, b);
+        return dry.used;
+    })));
     Carver cv{static_cast<char*>(ws), 0};
     carve_sub(cv, g, cell->n_occ, nr, o, b);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1571,13 +1593,16 @@ int rpa_energy(int32_t ncell, const rpa_cell* cells, const int32_t* nr, int32_t 
             return fail(RPA_EINVAL, "nr must be in [1, min(4096, N_d)]");
         if (!V0[c]) return fail(RPA_EINVAL, "V0 pointer is NULL");
     }
-    const std::vector<Opts> copt = cell_options(ncell, cells, nr, nfreq, o);
+    std::vector<Opts> copt;
     // each cell works in its own slice of the workspace (256-byte aligned offsets)
     std::vector<size_t> offs(ncell + 1, 0);
-    for (int c = 0; c < ncell; ++c)
-        offs[c + 1] = offs[c] + energy_cell_bytes(grid_of(&cells[c]), cells[c].n_occ, nr[c], nfreq,
-                                                  copt[c]);
-    RPA_CHECK(check_ws(ws, ws_bytes, offs[ncell]));
+    RPA_CHECK(check_ws(ws, ws_bytes, fit_ws(ws_bytes, &o, [&](const Opts& p) {
+        copt = cell_options(ncell, cells, nr, nfreq, p);
+        for (int c = 0; c < ncell; ++c)
+            offs[c + 1] = offs[c] + energy_cell_bytes(grid_of(&cells[c]), cells[c].n_occ, nr[c],
+                                                      nfreq, copt[c]);
+        return offs[ncell];
+    })));
     hipStream_t s = static_cast<hipStream_t>(stream);
     std::vector<CellRun> run(ncell);
     for (int c = 0; c < ncell; ++c) {
@@ -1645,10 +1670,12 @@ int rpa_energy_backward(const rpa_cell* cell, int32_t nfreq, const double* omega
     Opts o;
     RPA_CHECK(read_opts(opt, &o));
     RPA_CHECK(check_solver_geometry(cell, o));
-    Carver dry;
     BackBuf b;
-    carve_back(dry, g, cell->n_occ, nr, o, b);
-    RPA_CHECK(check_ws(ws, ws_bytes, dry.used));
+    RPA_CHECK(check_ws(ws, ws_bytes, fit_ws(ws_bytes, &o, [&](const Opts& p) {
+        Carver dry;
+        carve_back(dry, g, cell->n_occ, nr, p, b);
+        return dry.used;
+    })));
     Carver cv{static_cast<char*>(ws), 0};
     carve_back(cv, g, cell->n_occ, nr, o, b);
     hipStream_t s = static_cast<hipStream_t>(stream);

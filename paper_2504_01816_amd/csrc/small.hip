@@ -969,7 +969,7 @@ hipError_t launch_energy_logdet(int m, const double* C, double* work, double* ou
 hipError_t launch_syevj(int m, const double* A, double* work, double* w, double* Y,
                         hipStream_t s) {
     if (!Y) {
-        // eigenvalues alone; work holds 2 m^2 doubles
+        // eigenvalues alone; beyond kTriLds m^2 + 6 m + 4 doubles of work
         if (m <= kTriLds) {
             const size_t sh = (size_t(m) * (m + 1) + 3 * size_t(m)) * sizeof(double);
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(syev_lds_kernel),
