@@ -76,7 +76,8 @@ struct Opts {
                                  // below: the library default, or a cell's share of it)
     bool precond = false;        // RPA_FLAG_PRECOND
     int block = 0;               // cocg_block: block COCG width (0, 1: off)
-    bool lean = false;           // the caller's workspace holds only the least state (fit_ws)
+    bool lean = false;           // the workspace holds only the least state (fit_ws), or cells
+                                 // share the budget for it
     // the host-driven solver (split vectors): preconditioned or block COCG
     bool host_driven() const { return precond || block >= 2; }
 };
@@ -1220,7 +1221,11 @@ std::vector<Opts> cell_options(int ncell, const rpa_cell* cells, const int32_t* 
         sum += full[c];
     }
     if (sum <= kStateBudget) return out;
-    for (int c = 0; c < ncell; ++c) out[c].state_budget = kStateBudget * full[c] / sum;
+    for (int c = 0; c < ncell; ++c) {
+        out[c].state_budget = kStateBudget * full[c] / sum;
+        // many cells with few systems each would add up: 88 GB for 128 of 40^3
+        out[c].lean = true;
+    }
     return out;
 }
 

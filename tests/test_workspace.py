@@ -88,6 +88,21 @@ def test_least_state_is_accepted(op, n, ns, nv, opts, least):
     assert call(so, op, c, ns, nv, opts, ptr, 0x10000000, int(0.8 * least), None) == L.RPA_EWORKSPACE
 
 
+@pytest.mark.parametrize("n,ns,nr,ncell,gib", [(48, 64, 256, 64, 204.44), (32, 28, 112, 200, 159.08),
+                                               (40, 36, 36, 128, 137.02)])
+def test_cells_that_share_the_budget_keep_to_it(n, ns, nr, ncell, gib):
+    # many concurrent cells, each with few systems in flight: the longer rings are not added to the
+    # 128 GiB of state that they share (gib: the whole workspace without them)
+    cells = (L.RpaCell * ncell)()
+    for c in cells:
+        c.n[0] = c.n[1] = c.n[2] = n
+        c.n_occ, c.h = ns, 0.4
+    out = ctypes.c_size_t(0)
+    assert L.load().rpa_workspace_size(L.RPA_OP_ENERGY, ncell, cells, (ctypes.c_int32 * ncell)(*[nr] * ncell),
+                                       8, None, ctypes.byref(out)) == 0
+    assert out.value <= 1.03 * gib * 2 ** 30, out.value / 2 ** 30
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("op,n,ns,nv,opts,least", LEAST)
 def test_least_state_gives_the_same_results(op, n, ns, nv, opts, least):
