@@ -112,13 +112,13 @@ def test_least_state_gives_the_same_results(op, n, ns, nv, opts, least):
     c = dc.c_struct()
     rng = np.random.default_rng(22)
     nd = dc.nd
-    blocks = [np.linalg.qr(rng.standard_normal((nd, nv)))[0].T for _ in range(2)]
+    blocks = np.ascontiguousarray([np.linalg.qr(rng.standard_normal((nd, nv)))[0].T for _ in range(2)])
     Q = np.linalg.qr(rng.standard_normal((nv, nv)))[0]
     Cm = (Q * -np.linspace(0.1, 0.4, nv)) @ Q.T
     full = api.workspace_size(op, dc, nv, 2, L.default_options(**opts))
     outs = []
     for ws_bytes in (full, min(full, least)):
-        args = [torch.tensor(np.stack(blocks), device=dev),
+        args = [torch.tensor(blocks, device=dev),
                 torch.full((max(nv * nd, 2 * nv * nv),), float("nan"), dtype=torch.float64, device=dev),
                 torch.tensor(np.stack([0.5 * (Cm + Cm.T)] * 2), device=dev)]
         # the workspace holds not-a-numbers and 64 KiB behind it that have to stay
