@@ -7,6 +7,7 @@ import torch
 
 from oracle import coulomb as ocoul
 from oracle import precond as opre
+from oracle.block import chi0_apply_block
 from paper_2504_01816_amd import api, synth
 from paper_2504_01816_amd import lib as L
 from tests.test_gpu_real_form import chi0, make, rel
@@ -72,3 +73,16 @@ def test_coulomb_blocks_that_overlap(shape, nvec, fn):
         buf[a:a + n] = X.reshape(-1)
         out = fn(dc, buf[a:a + n].view(nvec, c.nd), 2, out=buf[b:b + n].view(nvec, c.nd))
         assert torch.equal(out, ref), shift
+
+
+def test_block_solver_with_the_gemm_preconditioner():
+    # an axis beyond 64 points: the preconditioner's GEMM passes under the block solver, two chunks
+    c = make((8, 65, 12), 3, 37)
+    U = np.random.default_rng(38).standard_normal((5, c.nd))
+    out, rc, st = chi0(c, U, 0.3, 1e-12, cocg_block=3, flags=L.RPA_FLAG_PRECOND, max_systems=9)
+    assert rc == 0 and st["cocg_launches"] == 2
+    for j0, j1 in ((0, 3), (3, 5)):
+        ref, _, _ = chi0_apply_block(U[j0:j1].T, c.vloc, c.psi.T, c.eps, 0.3, c.shape, c.h, 1e-12, 5000,
+                                     3, precond=True)
+        # two FP64 solvers that meet a residual of 1e-12 differ by cond(A) 1e-12 <= 1e-9 here
+        assert rel(out[j0:j1].T, ref) < 1e-9
