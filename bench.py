@@ -1,8 +1,8 @@
 """Benchmark of the RPA chi0 hot path on one MI355X.
 
 Default (--mode cycle): the 48^3 workload (64 Gaussian wells on a jittered lattice, N_s = 64,
-N_r = 256, 8 Gauss-Legendre frequencies, COCG tol 1e-8), complex64 COCG state with float64
-reliable updates.  A step is one pass of the hot path at one frequency: one subspace
+N_r = 256, 8 Gauss-Legendre frequencies, COCG tol 1e-8), RPA_MIXED (FP64 real-form solves
+with an exact residual check on this grid).  A step is one pass of the hot path at one frequency: one subspace
 iteration (u = nu^{1/2} V, chi0 u by the projector and 16384 batched Sternheimer solves,
 Delta rho, R = nu^{1/2} chi0 u, the projected matrix and its Rayleigh-Ritz energy, Cholesky-QR)
 through rpa_subspace_iter; step k works on frequency k mod 8, every frequency keeping its own
@@ -19,6 +19,7 @@ line with the metric, the roofline of the dominant kernel (batched COCG) measure
 events on its own stream, and the CPU oracle timed on a bounded sample.
 """
 import argparse
+import ctypes
 import json
 import os
 import sys
@@ -32,49 +33,70 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # algorithmic bytes per grid point per COCG iteration: read and write x, r, p
 ALG_BYTES = {"fp64": 96.0, "mixed": 48.0}
-# bytes per grid point per iteration that the real-form kernels move by design: a sweep reads w and
-# v_k and writes v_{k+1} and w (32), a ring vector is read once more (8), complex p and x are read
-# and written once per 16 iterations (3); with v, w and V_loc in registers a ring vector is written
-# and read once (16), p and x once per 8 (6)
-REAL_FORM_BYTES = {"streaming": 43.0, "resident": 22.0}
+
+KERNELS = {None: "cocg_wg", "streaming": "rcocg_wg", "resident-ring": "ring_wg", "resident": "full_wg"}
 
 
-def real_form_kernel(precision, shape, min_omega):
-    """The real-form kernel that solves on a grid of this shape: "streaming", "resident", or None
-    where the complex kernels do (a complex64 recurrence at every frequency, planes beyond 48 x 48
-    points, a forced launch shape)."""
-    if (precision == "mixed" and min_omega <= 0.0) or "RPA_COCG_SHAPE" in os.environ:
-        return None
-    n0, n1, n2 = shape
-    if n0 * n1 > 2304:
-        return None
-    return "resident" if n0 * n1 <= 704 and n2 <= 26 else "streaming"
+def real_form_kernel(precision, shape, min_omega, nsys=1 << 20):
+    """(kind, ring): the real-form kernel that the library launches for nsys systems on a grid of this
+    shape, and the basis vectors that it keeps; (None, 0) where the complex kernels solve (a complex64
+    recurrence at every frequency, a plane without a shape, a forced launch shape)."""
+    from paper_2504_01816_amd import lib as L
+    if precision == "mixed" and min_omega <= 0.0:
+        return None, 0
+    ring = ctypes.c_int32(0)
+    # mixed: complex solutions, for the exact residual
+    kind = L.load().rpa_internal_real_form((ctypes.c_int32 * 3)(*shape), min(nsys, 1 << 20),
+                                           int(precision == "mixed"), ctypes.byref(ring))
+    return (None, "streaming", "resident-ring", "resident")[kind], ring.value
 
 
-def alg_bytes(precision, shape, min_omega):
-    """Algorithmic bytes per point and iteration of the kernel that runs."""
-    kind = real_form_kernel(precision, shape, min_omega)
-    return REAL_FORM_BYTES[kind] if kind else ALG_BYTES[precision]
+def alg_bytes(precision, shape, min_omega, nsys=1 << 20):
+    """Bytes per point and iteration that the kernel that runs moves by design.  Complex kernels: x, r,
+    p read and written.  Real form: a sweep reads w and v_k and writes v_{k+1} and w (32), a ring vector
+    is read once more (8), complex p and x are read and written once per ring; with v, w and V_loc in
+    registers a ring vector is written and read once (16) and the halves of the ring take turns; with p
+    and x there too nothing (b once in and x once out, whatever the iterations)."""
+    kind, ring = real_form_kernel(precision, shape, min_omega, nsys)
+    if kind is None:
+        return ALG_BYTES[precision]
+    px = 64.0 if precision == "mixed" else 48.0
+    return {"streaming": 40.0 + px / max(ring, 1), "resident-ring": 16.0 + 2 * px / max(ring, 1),
+            "resident": 0.0}[kind]
 
 
-def kernel_name(precision, shape, min_omega):
-    kind = real_form_kernel(precision, shape, min_omega)
+def kernel_name(precision, shape, min_omega, nsys=1 << 20):
+    kind, _ = real_form_kernel(precision, shape, min_omega, nsys)
     if kind:
-        return ("%s (batched COCG in its real Lanczos form, one workgroup per system)" %
-                {"streaming": "rcocg_wg", "resident": "ring_wg"}[kind])
+        return ("%s (batched COCG in its real Lanczos form, one workgroup per system)" % KERNELS[kind])
     return ("cocg_wg<%s> (batched COCG, one workgroup per system)" %
             ("float, float2" if precision == "mixed" else "double, double"))
 
 
-def host_driven_bytes(precond, block, shape):
+def cells_alg_bytes(precision, wl, min_omega):
+    """alg_bytes over the cells of a workload, weighted with their points times systems (the
+    statistics do not say which cell an iteration belongs to)."""
+    w = [c.nd * c.n_occ * nr for c, nr in zip(wl.cells, wl.n_r)]
+    b = [alg_bytes(precision, c.shape, min_omega) for c in wl.cells]
+    return sum(x * y for x, y in zip(w, b)) / sum(w)
+
+
+def solve_dtype(precision, shapes, min_omega):
+    """The compute dtype of the Sternheimer solves: complex64 recurrences run only in the mixed path
+    and where the real-form FP64 kernels do not take their place."""
+    c64 = precision == "mixed" and any(real_form_kernel(precision, s, min_omega)[0] is None for s in shapes)
+    return "c64+f64" if c64 else "c128"
+
+
+def host_driven_bytes(precond, block, shape, fused_axis=32):
     """Algorithmic HBM bytes per point and system-iteration of the host-driven solvers: the
     step (q = A p; with the x and r updates for single systems: 128 B) and its direction update
     (r^T z and p: 64 B), or the block kernels (q = A p 32 B, alpha step 128 B, beta step 80 B);
-    the preconditioner adds 32 B per pass: 3 fused passes for axes <= 32, else priced at the 7
-    of the general products (axes up to 64 take the fused passes as well)."""
+    the preconditioner adds 32 B per pass: 3 fused passes where every axis has at most fused_axis
+    points (64 in the library), else the 7 of the general products."""
     b = 240.0 if block >= 2 else 192.0
     if precond:
-        b += 32.0 * (3 if max(shape) <= 32 else 7)
+        b += 32.0 * (3 if max(shape) <= fused_axis else 7)
     return b
 
 
@@ -341,13 +363,14 @@ def run_cycle(args):
         launches = len(rsteps)
         # a mixed step below mixed_min_omega runs the FP64 kernel
         shape, lowest = wl.cells[0].shape, min_om if p == "mixed" else 0.0
-        alg_pp = alg_bytes(p, shape, lowest)
+        nsys = c.n_occ * nr
+        alg_pp = alg_bytes(p, shape, lowest, nsys)
         achieved = alg_pp * pit / (cocg_ms * 1e-3) / 1e9 if cocg_ms > 0 else 0.0
         avg_ms = cocg_ms / max(1, launches)
         traffic, tb = cocg_traffic(wl.name, p, pit / max(1, launches))
         entry = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                  "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                 "kernel": kernel_name(p, shape, lowest),
+                 "kernel": kernel_name(p, shape, lowest, nsys),
                  "launches": launches, "avg_launch_ms": avg_ms,
                  "launch_omegas": ["%.4g" % wl.omegas[s["m"]] for s in rsteps],
                  # this kernel's dispatches of the timed region within the whole run, in
@@ -377,7 +400,7 @@ def run_cycle(args):
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": 1e3 * T / args.steps,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "c128" if args.precision == "fp64" else "c64+f64",
+        "dtype": solve_dtype(args.precision, [c.shape], min_om),
         "data": "synthetic",
         "config": {"workload": wl.name, "grid": list(c.shape), "h": c.h, "n_occ": c.n_occ,
                    "n_r": nr, "n_freq": nf, "cocg_tol": wl.cocg_tol,
@@ -532,9 +555,9 @@ def run_energy(args):
     pit = sum(s["point_iters"] for s in steps)
     launches = sum(s["launches"] for s in steps)
     min_om = opts.get("mixed_min_omega", L.default_options().mixed_min_omega)
-    alg_pp = alg_bytes(args.precision, wl.cells[0].shape, min_om)
+    alg_pp = cells_alg_bytes(args.precision, wl, min_om)
     if args.precond or args.block >= 2:
-        alg_pp = host_driven_bytes(args.precond, args.block, wl.cells[0].shape)
+        alg_pp = host_driven_bytes(args.precond, args.block, wl.cells[0].shape, fused_axis=64)
     alg = alg_pp * pit
     achieved = alg / (cocg_ms * 1e-3) / 1e9 if cocg_ms > 0 else 0.0
     avg_ms = cocg_ms / max(1, launches)
@@ -547,7 +570,7 @@ def run_energy(args):
         timing = ("forward wall time (cells one after another)" if args.cells_sequential
                   else "forward wall time (concurrent cells)")
     traffic, tb = cocg_traffic(wl.name, args.precision, pit / max(1, launches))
-    kernel = kernel_name(args.precision, wl.cells[0].shape, min_om)
+    kernel = "; ".join(dict.fromkeys(kernel_name(args.precision, x.shape, min_om) for x in wl.cells))
 
     def converged(iters):
         return subspace_converged(iters, opts["ec_tol"], opts["subspace_iters"])
@@ -567,7 +590,7 @@ def run_energy(args):
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": 1e3 * T / args.steps,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "c128" if args.precision == "fp64" else "c64+f64",
+        "dtype": solve_dtype(args.precision, [x.shape for x in wl.cells], min_om),
         "data": "synthetic",
         "config": {"workload": wl.name, "grid": list(wl.cells[0].shape), "h": wl.cells[0].h,
                    "n_occ": wl.cells[0].n_occ, "n_r": wl.n_r[0], "n_freq": len(wl.omegas),
@@ -614,7 +637,7 @@ def run_energy(args):
             "E_c": s2["E"], "subspace_iters": s2["iters"], "converged": converged(s2["iters"]),
             "time_to_ec_label": label(s2["iters"]),
             "E_c_rel_diff": [abs(a - b) / abs(b) for a, b in zip(s2["E"], steps[-1]["E"])],
-            "cocg_alg_GBs": alg_bytes(other, wl.cells[0].shape, min_om) * s2["point_iters"] / (s2["cocg_ms"] * 1e-3) / 1e9,
+            "cocg_alg_GBs": cells_alg_bytes(other, wl, min_om) * s2["point_iters"] / (s2["cocg_ms"] * 1e-3) / 1e9,
             "time_to_ec_ratio_vs_main": s2["fwd_s"] / out["time_to_ec_s"],
         }
         print("[bench] compare %s: %.2f s fwd, %.2f applies/s, E_c %s" % (

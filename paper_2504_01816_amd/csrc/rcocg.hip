@@ -2,12 +2,14 @@
 // rres_kernel.h).
 //
 // Grids whose columns and plane fit the registers of one workgroup take a resident kernel
-// (choose_resident).  Elsewhere the vectors stream, and a shape is (C rows per thread, Z planes per barrier step).  One row per thread up to 1024
-// columns: more rows share LDS reads, but the kernel waits on memory and wants waves (24^3: 26.5
-// ms with C = 1, 34 with 2, 47 with 3).  Two planes per step where n2 is even (26.5 against 28.8
-// ms).  Planes over 1024 points take the fewest rows that fit 1024 threads (40^3: 37.2 ms with C =
-// 2, 40.3 with 3), with one plane per step (two spill: 77 ms).  Planes over 2304 points (and over
-// 2048 unless three rows of 768 threads hold them) have no shape and stay on the complex kernel.
+// (choose_resident).  Elsewhere the vectors stream, and a shape is (C rows per thread, Z planes per
+// barrier step).  One row per thread up to 1024 columns: more rows share LDS reads, but the kernel
+// waits on memory and wants waves (24^3: 26.5 ms with C = 1, 34 with 2, 47 with 3).  Two planes per
+// step where n2 is even (26.5 against 28.8 ms).  Planes over 1024 points take the fewest rows that
+// fit their threads (40^3: 37.2 ms with C = 2, 40.3 with 3), with one plane per step (two spill: 77
+// ms).  So a plane has a shape if n0 n1 <= 1024, n0 ceil(n1 / 2) <= 1024 or n0 ceil(n1 / 3) <= 768
+// (all of these fit LDS); others stay on the complex kernel: every plane over 2304 points, but also
+// 36 x 64, 46 x 49 and 257 x 7.
 // RPA_RCOCG_SHAPE="C,Z" forces a streaming shape; RPA_COCG_VERBOSE=1 prints the one launched.
 #include <algorithm>
 #include <cstdio>
@@ -154,10 +156,42 @@ size_t rcocg_pool_bytes(const Grid& g, int nsys) {
     return need * vec;
 }
 
+namespace {
+
+// A launch on nsys systems with a pool of pool_bytes.  kind: 0 no shape, 1 streaming, 2 resident with
+// a ring, 3 resident with p and x in registers.
+struct Plan {
+    Shape s;
+    KernelFn fn = nullptr;
+    int kind = 0, bs = 0, grid = 0, ring = 0;
+    size_t lds = 0;
+};
+
+Plan make_plan(const Grid& g, int nsys, bool x_complex, size_t pool_bytes) {
+    Plan p;
+    p.s = choose(g);
+    if (!p.s.v) return p;
+    const size_t vec = size_t(g.nd()) * sizeof(double);
+    const Resident res =
+        choose_resident(g, x_complex, int(pool_bytes / (size_t(std::min(nsys, kCUs)) * vec)));
+    p.fn = res.fn ? res.fn : x_complex ? p.s.v->cplx : p.s.v->real;
+    p.kind = res.full ? 3 : res.fn ? 2 : 1;
+    p.grid = std::min(nsys, kCUs * (res.fn ? res.per_cu : per_cu(p.s.bs)));
+    p.lds = res.fn ? res.lds : p.s.lds;
+    p.bs = res.fn ? res.bs : p.s.bs;
+    p.ring = res.fn ? 2 * res.half
+                    : std::min(rcocg::kRingLong,
+                               int(pool_bytes / (size_t(p.grid) * vec)) - rcocg::kSlotExtra);
+    return p;
+}
+
+}  // namespace
+
 hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
     if (L.nsys <= 0) return hipSuccess;
-    const Shape s = choose(L.g);
-    if (!s.v) return hipErrorInvalidConfiguration;
+    const Plan p = make_plan(L.g, L.nsys, L.x_complex, L.pool_bytes);
+    if (!p.fn) return hipErrorInvalidConfiguration;
+    if (p.kind == 1 && p.ring < rcocg::kRingMin) return hipErrorInvalidValue;
     rcocg::Args a{};
     a.n0 = L.g.n0;
     a.n1 = L.g.n1;
@@ -182,27 +216,20 @@ hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t st) {
     a.iters = L.iters;
     a.status = L.status;
     a.refinements = L.refinements;
-    a.nbuf = s.nbuf;
-    a.rs = s.rs;
+    a.nbuf = p.s.nbuf;
+    a.rs = p.s.rs;
     a.periodic = L.g.periodic() ? 1 : 0;
-    const size_t vec = size_t(a.nd) * sizeof(double);
-    const Resident res = choose_resident(
-        L.g, L.x_complex, int(L.pool_bytes / (size_t(std::min(L.nsys, kCUs)) * vec)));
-    const KernelFn fn = res.fn ? res.fn : L.x_complex ? s.v->cplx : s.v->real;
-    const int grid = std::min(L.nsys, kCUs * (res.fn ? res.per_cu : per_cu(s.bs)));
-    const size_t lds = res.fn ? res.lds : s.lds;
-    const int bs = res.fn ? res.bs : s.bs;
-    a.ring = res.fn ? 2 * res.half
-                    : std::min(rcocg::kRingLong, int(L.pool_bytes / (size_t(grid) * vec)) - rcocg::kSlotExtra);
-    if (!res.fn && a.ring < rcocg::kRingMin) return hipErrorInvalidValue;
-    if (std::getenv("RPA_COCG_VERBOSE"))
+    a.ring = p.ring;
+    if (std::getenv("RPA_COCG_VERBOSE")) {
+        const char* const kinds[] = {"", "streaming", "resident-ring", "resident"};
         std::fprintf(stderr, "rcocg shape %s C=%d Z=%d bs=%d grid=%d ring=%d lds=%zu\n",
-                     res.full ? "resident" : res.fn ? "resident-ring" : "streaming",
-                     res.fn ? 1 : s.v->C, res.fn ? 2 * rres::kPairs : s.v->Z, bs, grid, a.ring, lds);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+                     kinds[p.kind], p.kind > 1 ? 1 : p.s.v->C, p.kind > 1 ? 2 * rres::kPairs : p.s.v->Z,
+                     p.bs, p.grid, p.ring, p.lds);
+    }
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(p.fn),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(p.lds));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(bs), lds, st, a);
+    hipLaunchKernelGGL(p.fn, dim3(p.grid), dim3(p.bs), p.lds, st, a);
     return hipGetLastError();
 }
 
@@ -257,3 +284,15 @@ hipError_t launch_residual_check(const RcocgLaunch& L, double* b2, hipStream_t s
 }
 
 }  // namespace rpa
+
+// For bench.py and the tests: which kernel solves on a grid, and the ring it keeps, where the
+// workspace is that of the size query.
+extern "C" int rpa_internal_real_form(const int32_t* n, int32_t nsys, int32_t x_complex, int32_t* ring) {
+    const rpa::Grid g{n[0], n[1], n[2], 1.0, 0};
+    if (rpa::cocg_shape_forced()) return 0;
+    const size_t state = size_t(nsys) * g.nd() * 40;
+    const rpa::Plan p =
+        rpa::make_plan(g, nsys, x_complex != 0, std::max(state, rpa::rcocg_pool_bytes(g, nsys)));
+    *ring = p.ring;
+    return p.kind;
+}

@@ -54,3 +54,29 @@ def test_cycle_steps_below_mixed_min_omega_run_the_fp64_kernel():
     assert b.cycle_kernel_class(0.2, "mixed", 0.2) == "mixed"
     assert b.cycle_kernel_class(0.1132, "mixed", 0.2) == "fp64"
     assert b.cycle_kernel_class(0.0203, "fp64", 0.0) == "fp64"
+
+
+def test_real_form_kernels_are_priced_as_the_library_launches_them():
+    # shapes at the edges of the launch rule; (None, 0): the complex kernels
+    b = _bench()
+    for shape, kind in (((12, 12, 12), "resident"), ((20, 20, 20), "resident"),
+                        ((24, 24, 24), "resident-ring"), ((20, 22, 32), "resident-ring"),
+                        ((26, 27, 26), "resident-ring"), ((32, 32, 32), "streaming"),
+                        ((48, 48, 48), "streaming"), ((12, 12, 33), "streaming"), ((36, 64, 12), None),
+                        ((46, 49, 12), None), ((30, 76, 12), None), ((257, 7, 12), None),
+                        ((52, 50, 12), None)):
+        assert b.real_form_kernel("fp64", shape, 0.0)[0] == kind, shape
+    # real and complex solutions of a short column take different kernels
+    assert b.real_form_kernel("mixed", (20, 20, 20), 0.2)[0] == "resident-ring"
+    assert b.real_form_kernel("mixed", (48, 48, 48), 0.0) == (None, 0)
+    assert b.alg_bytes("fp64", (48, 48, 48), 0.0) == 43.0       # ring of 16: 32 + 8 + 48 / 16
+    assert b.alg_bytes("mixed", (48, 48, 48), 0.2) == 44.0      # complex x: 64 / 16
+    assert b.alg_bytes("fp64", (24, 24, 24), 0.0) == 22.0       # halves of 8: 16 + 48 / 8
+    assert b.alg_bytes("fp64", (20, 20, 20), 0.0) == 0.0
+    assert b.alg_bytes("fp64", (52, 50, 12), 0.0) == 96.0
+    assert b.solve_dtype("mixed", [(48, 48, 48)], 0.2) == "c128"
+    assert b.solve_dtype("mixed", [(48, 48, 48)], 0.0) == "c64+f64"
+    assert b.solve_dtype("mixed", [(48, 48, 48), (52, 50, 12)], 0.2) == "c64+f64"
+    # the library's fused preconditioner passes reach axes of 64 points
+    assert b.host_driven_bytes(True, 0, (48, 48, 48), fused_axis=64) == 192.0 + 3 * 32.0
+    assert b.host_driven_bytes(True, 0, (65, 8, 12), fused_axis=64) == 192.0 + 7 * 32.0
