@@ -6,6 +6,10 @@ the COCG kernel's own HIP-event time reported in rpa_stats, and writes the faste
 (precision, grid) to a tuning file that the library reads (RPA_TUNE_FILE, default
 cocg_shapes.txt next to the shared library).
 
+It tunes the complex kernel.  By default that solves planes without a real-form shape (rcocg.hip),
+the continuations of RPA_MIXED, and every grid in RPA_MIXED with mixed_min_omega = 0; elsewhere the
+real-form kernels run and have no tuned shapes, so a tuning file changes nothing there.
+
 Usage: python -m paper_2504_01816_amd.autotune --config 1 [--precision fp64|mixed]
 """
 import argparse

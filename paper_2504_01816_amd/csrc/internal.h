@@ -164,15 +164,14 @@ struct RcocgLaunch {
     const double* rhs;      // nsys x N_d real
     void* x;                // nsys x N_d real (complex if x_complex)
     bool x_complex;
-    double* pool;           // solver state: rcocg_slots() slots
+    double* pool;           // solver state, of pool_bytes bytes
     size_t pool_bytes;
     int *iters, *status, *refinements;   // nsys (refinements: written 0, may be null)
 };
 hipError_t launch_rcocg(const RcocgLaunch& L, hipStream_t s);
 // After a real-form solve with complex solutions: b - A x in float64.  launch_residual writes it
 // (interleaved) for the systems order[0 .. nsys); launch_residual_check compares it with tol |b|
-// for every system: status 0 becomes 1 where it is larger, refinements is 1, b2 = |b|^2.  The pool
-// is its scratch.
+// for every system: status 0 becomes 1 where it is larger, refinements is 1, b2 = |b|^2.
 hipError_t launch_residual(const RcocgLaunch& L, double* r, hipStream_t s);
 hipError_t launch_residual_check(const RcocgLaunch& L, double* b2, hipStream_t s);
 // Host-only: whether a launch shape exists for the grid, and the bytes of state pool for nsys

@@ -16,8 +16,8 @@
 // workgroup per system on the plain kernel's z-march (pc_step_wg; pc_step, which gathers
 // the 36 neighbours through the caches, where no march shape fits); pc_rz does r^T z and the
 // p update; reductions are workgroup-local and in a fixed order.  z = M r is three
-// LDS-staged passes (x-y planes forward, z pencils with the diagonal scale, x-y planes
-// inverse) over all systems at once for axes up to 64 points, else 3 + 3 Kronecker GEMM passes with a
+// passes on the matrix cores (kron.hip: x-y planes forward, z columns with the diagonal scale, x-y
+// planes back) over all systems at once for axes up to 64 points, else 3 + 3 Kronecker GEMM passes with a
 // diagonal scale.  Every thread touches the same points in both loops of a kernel, so a
 // value a thread writes is read back only by itself.  Converged systems drop out of the
 // per-system kernels; the host tests for the end every few iterations.
@@ -849,7 +849,8 @@ hipError_t launch_vloc_mean(int64_t nd, const double* vloc, double* out, hipStre
 // 21.4 and 16.3 at 36^3 (128), 13.5 and 11.5 at 64 x 64 x 16 (64); at 24^3 (1024 systems) the fused
 // passes on the vector units took 41.5 ms, on the matrix cores 32.5.
 hipError_t apply_precond(const PcocgLaunch& L, int nsys, hipStream_t s) {
-    // RPA_PRECOND_PASSES=gemm forces the GEMM passes (for measurements)
+    // RPA_PRECOND_PASSES=gemm forces the GEMM passes (for measurements); "lds", which once asked for
+    // the fused passes beyond their default range, has nothing left to ask for
     static const char* force = std::getenv("RPA_PRECOND_PASSES");
     const bool gemm = force && std::strcmp(force, "gemm") == 0;
     if (kron_fused_fits(L.g) && !gemm)

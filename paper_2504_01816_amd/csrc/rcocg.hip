@@ -4,12 +4,13 @@
 // Grids whose columns and plane fit the registers of one workgroup take a resident kernel
 // (choose_resident).  Elsewhere the vectors stream, and a shape is (C rows per thread, Z planes per
 // barrier step).  One row per thread up to 1024 columns: more rows share LDS reads, but the kernel
-// waits on memory and wants waves (24^3: 26.5 ms with C = 1, 34 with 2, 47 with 3).  Two planes per
-// step where n2 is even (26.5 against 28.8 ms).  Planes over 1024 points take the fewest rows that
-// fit their threads (40^3: 37.2 ms with C = 2, 40.3 with 3), with one plane per step (two spill: 77
-// ms).  So a plane has a shape if n0 n1 <= 1024, n0 ceil(n1 / 2) <= 1024 or n0 ceil(n1 / 3) <= 768
-// (all of these fit LDS); others stay on the complex kernel: every plane over 2304 points, but also
-// 36 x 64, 46 x 49 and 257 x 7.
+// waits on memory and wants waves (24^3, ring of 8: 26.5 ms with C = 1, 34 with 2, 47 with 3).  Two
+// planes per step where n2 is even (26.5 against 28.8 ms).  Planes over 1024 points take the fewest
+// rows that fit their threads (40^3: 37.2 ms with C = 2, 40.3 with 3), with one plane per step (two
+// spill: 77 ms; with one, three rows in 768 threads spill 33 registers outside the plane loop).
+// So a plane has a shape if n0 n1 <= 1024, n0 ceil(n1 / 2) <= 1024 or n0 ceil(n1 / 3) <= 768 (all of
+// these fit LDS); others stay on the complex kernel: every plane over 2304 points, but also 36 x 64,
+// 46 x 49 and 257 x 7.
 // RPA_RCOCG_SHAPE="C,Z" forces a streaming shape; RPA_COCG_VERBOSE=1 prints the one launched.
 #include <algorithm>
 #include <cstdio>
@@ -101,6 +102,11 @@ constexpr int kCUs = 256;
 
 // The register-resident kernels where a column and the plane fit (see their instances): real
 // solutions with p and x in registers, else with p and x in memory and up to four waves that fold.
+// They are taken up to the last shape that fits, where one wave is left to fold and registers spill:
+// streaming is slower there too.  Kernel ms for 1024 and 8 systems, resident, streaming (and the complex
+// kernel): 26 x 27 x 26 10.9 and 2.19, 12.4 and 2.85 (34.1, 7.4); 26 x 27 x 14 4.6 and 1.10, 6.8 and
+// 1.59; 25 x 28 x 24 8.5 and 1.82, 11.4 and 2.69; 22 x 27 x 25 7.8 and 1.54, 11.3 and 2.91;
+// 20 x 22 x 32 6.3 and 1.47, 11.2 and 2.72; 21 x 21 x 32 6.4 and 1.47, 11.3 and 2.70.
 struct Resident {
     KernelFn fn = nullptr;
     bool full = false;

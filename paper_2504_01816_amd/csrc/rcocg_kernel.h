@@ -32,8 +32,9 @@
 //    are bitwise reproducible, whatever slot, ring or launch a system gets.
 //
 // Measured, chi0 block-applies, the two-sweep complex kernel against this one: 24^3, 1024
-// systems, omega 0.02, tol 1e-10: 62.2 -> 26.5 ms (5.4 TB/s); 48^3, 1024 systems, omega 8.8, tol
-// 1e-8: 136 -> 42 ms; 32^3, 2 x 1024 systems with complex solutions: 217 -> 81 ms.
+// systems, omega 0.02, tol 1e-10: 62.2 -> 24.3 ms; 48^3, 1024 systems, omega 8.8, tol 1e-8: 136 ->
+// 42 ms; 32^3, 2 x 1024 systems with complex solutions: 217 -> 81 ms.  At 48^3, 16384 systems, omega
+// 0.11 counters give 48.6 B per point-iteration (43 by design), at 5.6 TB/s.
 #pragma once
 
 #include <type_traits>
@@ -448,19 +449,14 @@ struct Recurrence {
 // p <- v_j - l_j p, x <- x + e_j p (e = zeta / d) over the m newest basis vectors, in order: the
 // same operations on every point however many steps one update takes, so a solve's bits do not
 // depend on the ring.  The first update starts from x = 0, p = 0, and scales v_1, which is stored
-// as b, by s1 = 1 / |b|.  p is not stored at the end of a solve (done).
-// REG: the coefficients in registers (else read from LDS at every point).
-template <typename XS, bool REG, int M>
+// as b, by s1 = 1 / |b|.  p is not stored at the end of a solve (done).  The coefficients are read
+// from LDS at every point: in registers they spilled (48^3: 77 ms against 42, ring of 16).
+template <typename XS, int M>
 __device__ __forceinline__ void update_px(int64_t nd, const double* ring, double2* p, XS* x,
                                           const Coef* coef, int m, bool first, double s1,
                                           bool done) {
     constexpr bool CX = std::is_same<XS, double2>::value;
     const unsigned n = unsigned(nd);
-    Coef cr[REG ? M : 1];
-    if constexpr (REG) {
-#pragma unroll
-        for (int j = 0; j < M; ++j) cr[j] = coef[j < m ? j : 0];
-    }
     for (unsigned i = threadIdx.x; i < n; i += blockDim.x) {
         double v[M];
 #pragma unroll
@@ -483,8 +479,8 @@ __device__ __forceinline__ void update_px(int64_t nd, const double* ring, double
 #pragma unroll
         for (int j = 0; j < M; ++j) {
             if (j < m) {
-                if constexpr (!REG) asm volatile("" ::: "memory");
-                const Coef c = REG ? cr[REG ? j : 0] : coef[j];
+                asm volatile("" ::: "memory");
+                const Coef c = coef[j];
                 const double pr = v[j] - c.lr * pv.x + c.li * pv.y;
                 pv.y = -c.lr * pv.y - c.li * pv.x;
                 pv.x = pr;
@@ -566,7 +562,7 @@ void rcocg_wg(Args a) {
             if (slot == a.ring) slot = 0;
             if (rc.done || slot == 0) {
                 global_barrier();
-                update_px<XS, false, kRingLong>(a.nd, ring, p, x, coef, m, px_first, rc.ibn, rc.done);
+                update_px<XS, kRingLong>(a.nd, ring, p, x, coef, m, px_first, rc.ibn, rc.done);
                 px_first = false;
                 carry = false;              // the queue's registers are free for the update
 #pragma unroll

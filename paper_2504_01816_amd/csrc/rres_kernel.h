@@ -2,20 +2,23 @@
 // workgroup: thread = column of the x-y plane, the column's n2 = NZ points of v_k and of w / v_{k-1}
 // in registers, every z neighbour a register of its own.
 //
-// What it removes: the streaming kernel moves 46 B per point-iteration, 32 of them w and v_k going
-// to memory and back between iterations, and so runs at the memory rate (24^3: 5.4 TB/s).  With
-// FULL p and x stay in registers as well and a solve touches memory only at its start and end; else
-// each v_k goes to the ring (8 B) and comes back once for the update of p and x (8 + 48 / m B).
+// What it removes: the streaming kernel moves 43 B per point-iteration, 32 of them w and v_k going
+// to memory and back between iterations, and so runs at the memory rate.  With FULL p and x stay in
+// registers as well and a solve touches memory only at its start and end (0.3 B per point-iteration
+// counted at 20^3); else each v_k goes to the ring (8 B) and comes back once for the update of p and x
+// (8 + 48 / m B; 24.7 counted at 24^3).
 // That update is done by waves of its own while the others sweep: the ring has two halves of m
 // vectors, one filled by the sweeps, one folded into p and x, a few elements per barrier step.
-// What bounds it: LDS, 24 neighbours of x and y per point.  Two planes are staged side by side, so
-// that one 16-byte read serves the points of both, with a row stride of n0 + 16 entries, free of
-// bank conflicts where a wave crosses a row end.
+// What bounds it: waits on LDS (24 neighbours of x and y per point) and on the barriers, 60% of the
+// waves' cycles at 24^3; LDS itself is busy in 39% of the CUs' cycles (40% at 20^3).  Two planes are
+// staged side by side, so that one 16-byte read serves the points of both, with a row stride of
+// n0 + 16 entries: bank conflicts are 0 (24^3) and 2.4% (20^3) of the LDS cycles.
 //
-// Measured, the streaming kernel against this one: 24^3, 1024 systems, omega 0.02, tol 1e-10: 27.0 ->
-// 17.5 ms, of which the sweeps alone are 12.0 (folding by the sweeping waves themselves, between
-// sweeps: 20.7); 20^3, 1024 systems, omega 1.4 (p and x in registers): 7.0 -> 3.5 ms; 12^3, 16
-// systems: 1.29 -> 0.68 ms; 22 x 27 x 25, 143 systems: 8.4 -> 5.3 ms.
+// Measured, calls with the streaming kernel against this one: 24^3, 1024 systems, omega 0.02, tol
+// 1e-10: 24.3 -> 16.7 ms (the fold by the sweeping waves themselves, between sweeps, took 3.2 more);
+// the same isolated, omega 0.31: 12.1 -> 8.8 ms; 20^3, 2048 systems over eight frequencies, twice (p
+// and x in registers): 39.2 -> 17.7 ms; 12^3, 16 systems: 1.25 -> 0.55 ms; 22 x 27 x 25, 143 systems:
+// 8.7 -> 5.0 ms.
 //
 // n2 is a template parameter because a register array needs constant indices; the rule that picks
 // this kernel (rcocg.hip) is the register budget of the column height and the workgroup.
@@ -490,7 +493,7 @@ void ring_wg(Args a) {
         } else {
             // the vectors since the last full half, by every wave
             global_barrier();
-            rcocg::update_px<X, false, kRing>(a.nd, ring + half * M * a.nd, p, x, coef + half * kRing, slot,
+            rcocg::update_px<X, kRing>(a.nd, ring + half * M * a.nd, p, x, coef + half * kRing, slot,
                                        none, rc.ibn, true);
         }
         finish(a, sys, rc);

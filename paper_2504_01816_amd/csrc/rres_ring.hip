@@ -4,8 +4,10 @@
 namespace rpa {
 namespace rres {
 
-// Four registers per point of the column (v, w) and about fifty more: 168 per thread (12 waves) hold
-// 26 points, 256 (8 waves) 32.
+// Four registers per point of the column (v, w) and about fifty more for the sweep; the fold's two
+// chunks want about as many, whatever the column.  With 12 waves (168 registers) every height from 12
+// to 26 spills 36 to 68 vector registers to scratch (halves of eight), with 8 waves (256) only 31 and
+// 32 points do, 2 to 10; 122 to 198 scalars are parked in vector lanes.
 KernelFn ring_variant(int nz, bool xc, int half) {
     // short halves only for complex solutions of the columns whose real ones full_wg takes
     if (half == kRingHalfMin && (!xc || nz > 20)) return nullptr;

@@ -514,7 +514,7 @@ __device__ double bisect(int m, const double* d, const double* e2, int t, double
     return 0.5 * (lo + hi);
 }
 
-// Gershgorin bracket of the tridiagonal, over the block; red: LDS, 16 doubles.
+// Gershgorin bracket of the tridiagonal, over the block; red: LDS, 48 doubles.
 __device__ void bracket(int m, const double* d, const double* e, double* red, double* lo,
                         double* hi, double* pivmin) {
     double a = INFINITY, b = -INFINITY, c = 0.0;

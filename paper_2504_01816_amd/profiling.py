@@ -32,6 +32,10 @@ KERNEL_SOURCES = ("csrc/cocg_kernel.h", "csrc/cocg.hip", "csrc/cocg_f64.hip", "c
                   "csrc/rcocg_kernel.h", "csrc/rcocg.hip", "csrc/rres_kernel.h", "csrc/rres_full.hip",
                   "csrc/rres_ring.hip")
 
+# the kernels of one COCG launch: the solvers (cocg_wg, rcocg_wg, ring_wg, full_wg) and the mixed
+# path's residual check
+COCG_KERNELS = ("cocg_wg", "ring_wg", "full_wg", "check_wg")
+
 
 def kernel_source_hash():
     """SHA-256 over the COCG kernel's sources: counters taken on other sources are stale."""
@@ -139,7 +143,8 @@ def _stage_flops(nd, n, ns, nr):
          2.0 * nd * ns * ns * nr),
         ("projected right-hand sides b' = b - Psi c (HBM-bound: writes the COCG start vectors)",
          "CoeffT", 2.0 * nd * ns * ns * nr),
-        ("nu^1/2 Kronecker transforms (2 applications x 6 passes; HBM-bound, n/8 flop/B)", "Axis",
+        ("nu^1/2 Kronecker transforms (2 applications x 3 fused or 6 product passes; HBM-bound)",
+         "kron_xy|kron_z|Axis",
          2 * sum(4.0 * a * nd * nr for a in n)),
         ("projection C = V^T R and Gram M = R^T R", "ColT", 2 * 2.0 * nd * nr * nr),
         ("Cholesky-QR rotation V = R L^-T", "SmallT", 2.0 * nd * nr * nr),
@@ -169,11 +174,12 @@ def cmd_stages(args):
         print("| %s | `%s` | %d | %.3f | %.3g | %.2f | %.1f%% |" % (
             name, key.replace("|", "`, `"), nds, t * 1e3, f, f / t / 1e12 if t else 0,
             100 * f / t / 78.6e12 if t else 0))
-    for key, label in (("cocg_wg", "COCG"), ("drho", "Delta rho"), ("reduce_parts", "split-K reductions"),
-                       ("energy_kernel", "energy (Cholesky of I - C)"), ("chol_inv", "Cholesky + inverse")):
-        ks = [k for k in dur if key in k]
+    for key, label in (("|".join(COCG_KERNELS), "COCG"), ("drho", "Delta rho"), ("reduce_parts", "split-K reductions"),
+                       ("energy_kernel", "energy (Cholesky of I - C)"),
+                       ("chol_kernel|tri_inv", "Cholesky + inverse")):
+        ks = [k for k in dur if any(part in k for part in key.split("|"))]
         t = sum(sum(dur[k]) for k in ks)
-        print("| %s | `%s` | %d | %.3f | | | |" % (label, key, sum(len(dur[k]) for k in ks), t * 1e3))
+        print("| %s | `%s` | %d | %.3f | | | |" % (label, key.replace("|", "`, `"), sum(len(dur[k]) for k in ks), t * 1e3))
 
 
 def cmd_gaps(args):
@@ -194,7 +200,7 @@ def cmd_gaps(args):
         a, b = int(r["Start_Timestamp"]), int(r["End_Timestamp"])
         d = (b - a) * 1e-6
         gap = max(0.0, (a - prev_end) * 1e-6) if prev_end is not None else 0.0
-        if "cocg_wg" in r["Kernel_Name"]:
+        if any(m in r["Kernel_Name"] for m in COCG_KERNELS):
             k_cocg += d
         else:
             k_other += d
@@ -266,7 +272,7 @@ def per_kernel_means(rows):
 
 
 def short(name, n=70):
-    name = name.replace("rpa::cocg::", "").replace("HIP_vector_type", "vec")
+    name = name.replace("rpa::cocg::", "").replace("rpa::rcocg::", "").replace("rpa::rres::", "").replace("HIP_vector_type", "vec")
     return name if len(name) <= n else name[: n - 3] + "..."
 
 
@@ -296,8 +302,8 @@ def cmd_kstats(args):
             float(r["Percentage"])))
 
 
-def _total(rows, match, counter):
-    return sum(v for k, c, v, _ in rows if match in k and c == counter)
+def _total(rows, counter):
+    return sum(v for k, c, v, _ in rows if c == counter and any(m in k for m in COCG_KERNELS))
 
 
 def cmd_traffic(args):
@@ -309,9 +315,9 @@ def cmd_traffic(args):
     for counter, copy_csv, apply_csv in (("FETCH_SIZE", args.copy_fetch, args.apply_fetch),
                                          ("WRITE_SIZE", args.copy_write, args.apply_write)):
         crow = read_counters(copy_csv)
-        cval = sum(v for k, c, v, _ in crow if c == counter and "cocg" not in k)
+        cval = sum(v for k, c, v, _ in crow if c == counter and "rpa::" not in k)
         factor = copy_bytes / (cval * 1024.0) if cval > 0 else float("nan")
-        aval = _total(read_counters(apply_csv), "cocg_wg", counter)
+        aval = _total(read_counters(apply_csv), counter)
         out[counter.lower() + "_copy_factor"] = factor
         out[counter.lower() + "_bytes_per_point_iter"] = aval * 1024.0 * factor / stats["cocg_point_iters"]
     out["bytes_per_point_iter"] = (out["fetch_size_bytes_per_point_iter"]
