@@ -198,7 +198,7 @@ int rpa_default_options(rpa_options* opt);
  *   bytes   host out
  * Calls that solve few systems (about 1000 or fewer) ask for more than the state named at
  * max_systems, for a longer ring of basis vectors per system.  They also accept a workspace
- * without it, down to that state and the blocks of the driver, and then run with a shorter
+ * without it, down to that state and their own blocks, and then run with a shorter
  * ring: slower, equal to rounding.
  */
 int rpa_workspace_size(int32_t op, int32_t ncell, const rpa_cell* cells, const int32_t* nvec,

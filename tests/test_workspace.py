@@ -1,5 +1,5 @@
 """Workspaces smaller than the size query's answer: the least state of a call (r, p, p', x of every
-system and the blocks of the driver, as the library asked for it before it kept longer rings of basis
+system and the call's own blocks, as the library asked for it before it kept longer rings of basis
 vectors for small launches) is accepted, and a call in it gives the same results to rounding."""
 import ctypes
 
